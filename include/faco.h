@@ -289,9 +289,11 @@ enum {
                                [10] copies, [11] backup/nearest choices; call
                                counts: [5] windows, [6] one-step choices, [7]
                                copies, [12] evaluation rounds, [13] ticks
-                               in Or-opt evaluation, [14] rounds that
-                               evaluated Or-opt, [15] ticks in the array
-                               rewrites of moves (part of [2]); segment
+                               in Or-opt evaluation (0 with several waves
+                               per ant: part of every round), [14] rounds
+                               that evaluated Or-opt, [15] ticks in the
+                               array rewrites of moves (part of [2], all of
+                               it with several waves per ant); segment
                                lists: [16] materialisations, [17] ticks in
                                them, [18] cities relabelled by splits, [19]
                                splits, [20] records passed by moves, [21]

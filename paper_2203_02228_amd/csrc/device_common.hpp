@@ -112,6 +112,7 @@ FACO_DEV int64_t wave_min_i64(int64_t v) { return wave_reduce_i64(v, OpMin()); }
 FACO_DEV int64_t wave_sum_i64(int64_t v) { return wave_reduce_i64(v, OpAdd()); }
 FACO_DEV int wave_sum_i32(int v) { return wave_reduce_i32(v, OpAdd()); }
 FACO_DEV int wave_min_i32(int v) { return wave_reduce_i32(v, OpMin()); }
+FACO_DEV int wave_max_i32(int v) { return wave_reduce_i32(v, OpMax()); }
 
 // A value every lane holds alike, moved to a scalar register: control flow
 // on it is a scalar branch (needed where a workgroup barrier follows).

@@ -59,6 +59,11 @@ FACO_DEV int wrapn(int q, int n) {
   }
   return q;
 }
+// for -n <= q < 2n
+FACO_DEV int wrapc(int q, int n) {
+  q += q < 0 ? n : 0;
+  return q >= n ? q - n : q;
+}
 // for 0 <= q < 2n
 FACO_DEV int wrap1(int q, int n) { return q >= n ? q - n : q; }
 
@@ -84,8 +89,7 @@ FACO_DEV int wrap_off(int q, int off, int n) {
 // ===================================================================== //
 constexpr int kMaxTeam = 8;
 enum TeamOp {
-  OP_EXIT = 0, OP_REVERSE = 1, OP_SHIFT = 2, OP_WINDOW = 3, OP_SWEEP = 4, OP_COPY = 5,
-  OP_NEAREST = 6, OP_OROPT = 7, OP_SEGPERM = 8, OP_SEGMAT = 9
+  OP_EXIT, OP_WINDOW, OP_SWEEP, OP_COPY, OP_NEAREST, OP_OROPT, OP_SEGPERM, OP_SEGMAT, OP_SEARCH
 };
 struct TeamLds {
   int op;
@@ -98,7 +102,14 @@ struct TeamLds {
   int cities[kMaxTeam * kWave];  // sweep: the batch of cities to test
   int disp[4];                   // persistent batches: the next task
   int64_t okey[kMaxTeam][4];     // Or-opt: per-wave maxima of each listed city
-  int orx[14][kWave];            // Or-opt: the leader's loaded neighbourhoods
+  union {
+    int orx[14][kWave];          // segment lists' Or-opt: the leader's loaded neighbourhoods
+    struct {                     // local search by all waves (team_local_search)
+      alignas(16) int desc[2][kMaxTeam * 32];  // each wave's best move, by round parity
+      int pushed;                // cities wave 0 listed after the move (bit 8: queue spilled)
+      int cnt[2];                // sweep: cities gathered, by pass parity
+    } ls;
+  };
   int sgs[4];                    // segment-list tour: live buffer, epoch, last move's records
   int sov[9];                    // segment-list move: link overrides
 };
@@ -950,7 +961,7 @@ FACO_DEV GroupEval eval_group(const Inst &I, uint32_t flags, int a, bool gvalid,
   const int d_ab = act ? I.cl_d[row + s] : 0;
   const int2 xa = I.xy[a];
   // level 2
-  const int pn = wrapn(pa + s - 3, n);
+  const int pn = wrapc(pa + (s < 7 ? s : 3) - 3, n);
   const int nb = s < 7 ? route[pn] : a;
   const int2 xnb = s < 7 ? rxy[pn] : xa;
   const int pb = pos[b];
@@ -1005,7 +1016,7 @@ FACO_DEV GroupEval eval_group_pre(const Inst &I, uint32_t flags, int a, bool gva
   const int pb = pos[b];
   const int2 xb = I.xy[b];
   // level 2
-  const int pn = wrapn(pa + s - 3, n);
+  const int pn = wrapc(pa + (s < 7 ? s : 3) - 3, n);
   const int nb = s < 7 ? route[pn] : a;
   const int2 xnb = s < 7 ? rxy[pn] : xa;
   const int pbs = pb + 1 == n ? 0 : pb + 1, pbp = pb == 0 ? n - 1 : pb - 1;
@@ -1075,24 +1086,24 @@ FACO_DEV void eval_group_oropt(const Inst &I, bool want, GroupEval &R,
     if (L > Lmax || !((slot_mask >> vi) & 1u)) continue;
     const int2 xf = grp_lane2<GS>(xnb, lf), xl = grp_lane2<GS>(xnb, ll);
     const int2 xo = dir == 0 ? xl : xf;
-    const int fpos = dir == 0 ? pa : wrapn(pa - L + 1, n);
+    const int fpos = dir == 0 ? pa : wrapc(pa - L + 1, n);
     // removal: (p, f) + (l, q) - (p, q); rem_a: the edge at a it removes
     const int rem_a = dir == 0 ? u[2] : u[3];
     const int g_rem = dir == 0 ? u[2] + u[2 + L] - u[5 + L]
                                : u[3 - L] + u[3] - (L == 2 ? u[9] : u[10]);
     if (!act) continue;
     if (!(d_ab < rem_a)) continue;
-    if (wrapn(pb - fpos, n) < L) continue;
+    if (wrapc(pb - fpos, n) < L) continue;
     // costs are >= 0: a variant whose gain without the new edge's cost
     // cannot beat lbest needs no cost
-    if (wrapn(pbs - fpos, n) >= L && g_rem + d_bs - d_ab > lbest) {
+    if (wrapc(pbs - fpos, n) >= L && g_rem + d_bs - d_ab > lbest) {
       const int g = g_rem + d_bs - d_ab - cost(xo, xbs);
       if (g > lbest) {
         lbest = g;
         lidx = (vi * K + s) * 2 + 0;
       }
     }
-    if (wrapn(pbp - fpos, n) >= L && g_rem + d_bp - d_ab > lbest) {
+    if (wrapc(pbp - fpos, n) >= L && g_rem + d_bp - d_ab > lbest) {
       const int g = g_rem + d_bp - d_ab - cost(xo, xbp);
       if (g > lbest) {
         lbest = g;
@@ -1159,8 +1170,8 @@ FACO_DEV Move extract_move(const Inst &I, const GroupEval &R, int j) {
   mv.e = side ? readlane_i(R.bp, l) : readlane_i(R.bs, l);
   mv.side = side;
   mv.pb = readlane_i(R.pb, l);
-  mv.fpos = dir == 0 ? pa : wrapn(pa - L + 1, n);
-  mv.pq = wrapn(mv.fpos + L, n);
+  mv.fpos = dir == 0 ? pa : wrapc(pa - L + 1, n);
+  mv.pq = wrapc(mv.fpos + L, n);
   mv.pp = mv.fpos == 0 ? n - 1 : mv.fpos - 1;
   mv.s0 = readlane_i(R.nb, base + lf);
   mv.s1 = readlane_i(R.nb, base + lf + (L > 1 ? 1 : 0));
@@ -1204,7 +1215,7 @@ FACO_DEV bool has_improving(const Inst &I, uint32_t flags, int x,
   int xnx[7], xny[7];
 #pragma unroll
   for (int j = 0; j < 7; ++j) {
-    const int2 q = rxy[wrapn(px + j - 3, n)];
+    const int2 q = rxy[wrapc(px + j - 3, n)];
     xnx[j] = q.x; xny[j] = q.y;
   }
 #define XN(j) make_int2(xnx[j], xny[j])
@@ -1222,7 +1233,7 @@ FACO_DEV bool has_improving(const Inst &I, uint32_t flags, int x,
     int dir, L, lf, ll, lp, lq;
     or_slot_lanes(vi, dir, L, lf, ll, lp, lq);
     sl[vi] = L;
-    sf[vi] = dir == 0 ? px : wrapn(px - L + 1, n);
+    sf[vi] = dir == 0 ? px : wrapc(px - L + 1, n);
     const int2 xo = dir == 0 ? XN(ll) : XN(lf);
     sox[vi] = xo.x;
     soy[vi] = xo.y;
@@ -1261,15 +1272,15 @@ FACO_DEV bool has_improving(const Inst &I, uint32_t flags, int x,
 #pragma unroll
         for (int vi = 0; vi < kOrSlots; ++vi) {
           const int L = sl[vi], fpos = sf[vi];
-          if (!found && d_xb < srem[vi] && wrapn(pb[j] - fpos, n) >= L) {
+          if (!found && d_xb < srem[vi] && wrapc(pb[j] - fpos, n) >= L) {
             const int2 xo = make_int2(sox[vi], soy[vi]);
             // costs are >= 0: no cost of the new edge is needed unless the
             // rest of the gain is positive
-            if (wrapn(pbs - fpos, n) >= L) {
+            if (wrapc(pbs - fpos, n) >= L) {
               const int rest = sg[vi] + es;
               if (rest > 0 && rest - cost(xo, xbs) > 0) found = true;
             }
-            if (wrapn(pbp - fpos, n) >= L) {
+            if (wrapc(pbp - fpos, n) >= L) {
               const int rest = sg[vi] + ep;
               if (rest > 0 && rest - cost(xo, xbp) > 0) found = true;
             }
@@ -1305,9 +1316,6 @@ FACO_DEV bool has_improving(const Inst &I, uint32_t flags, int x, const FlatT &T
 #include "faco_seg.hpp"
 
 constexpr int kChunks = 16;  // 64-element chunks in flight per wave and round
-// Rewrites of more pairs than this (elements, for block moves: twice this)
-// are shared by the team; shorter ones are the leader's alone.
-constexpr int kTeamMinPairs = 256;
 // Chunks in flight per wave of a team rewrite (one round covers
 // TW * kTeamChunks * 64 pairs).
 constexpr int kTeamChunks = 16;
@@ -1391,59 +1399,24 @@ FACO_DEV void shift_part(int n, int src, int dst, int D, bool down, int w, int32
   }
 }
 
-// Rewrites run by the leader alone when one round of its own covers them.
-template <int TW>
-FACO_DEV void team_reverse(int n, int s, int L, TeamLds *tl, int32_t *route, int32_t *pos,
-                           int2 *rxy) {
-  if (TW > 1 && (L >> 1) > kTeamMinPairs) {
-    team_post(tl, OP_REVERSE, s, L);
-    reverse_part<TW, kTeamChunks>(n, s, L, 0, route, pos, rxy);
-    team_sync();
-  } else if (TW > 1) {
-    reverse_part<1, kTeamMinPairs / kWave>(n, s, L, 0, route, pos, rxy);
-    wave_fence();
-  } else {
-    reverse_part<1>(n, s, L, 0, route, pos, rxy);
-    wave_fence();
-  }
-}
-template <int TW>
-FACO_DEV void team_shift(int n, int src, int dst, int D, bool down, TeamLds *tl,
-                         int32_t *route, int32_t *pos, int2 *rxy) {
-  if (TW > 1 && D > 2 * kTeamMinPairs) {
-    team_post(tl, OP_SHIFT, src, dst, D, down ? 1 : 0);
-    shift_part<TW, kTeamChunks>(n, src, dst, D, down, 0, route, pos, rxy);
-    team_sync();
-  } else if (TW > 1) {
-    shift_part<1, 2 * kTeamMinPairs / kWave>(n, src, dst, D, down, 0, route, pos, rxy);
-    wave_fence();
-  } else {
-    shift_part<1>(n, src, dst, D, down, 0, route, pos, rxy);
-    wave_fence();
-  }
-}
-
 // "Flip a section between x and y": the shorter of the paths x..y and z..w.
 // px, py, pz: array positions of x, y, z.
-template <int TW>
-FACO_DEV int apply_2opt(int n, int px, int py, int pz, TeamLds *tl, int32_t *route,
-                        int32_t *pos, int2 *rxy) {
-  const int L1 = wrapn(py - px, n) + 1;
-  if (2 * L1 <= n) {
-    team_reverse<TW>(n, px, L1, tl, route, pos, rxy);
-    return L1;
-  }
-  team_reverse<TW>(n, pz, n - L1, tl, route, pos, rxy);
-  return n - L1;
+FACO_DEV int apply_2opt(int n, int px, int py, int pz, int32_t *route, int32_t *pos,
+                        int2 *rxy) {
+  const int L1 = wrapc(py - px, n) + 1;
+  const bool first = 2 * L1 <= n;
+  const int L = first ? L1 : n - L1;
+  reverse_part<1>(n, first ? px : pz, L, 0, route, pos, rxy);
+  wave_fence();
+  return L;
 }
 
 // Or-opt: the segment and the shorter block between its old place and the
 // insertion edge exchange places (block keeps its orientation).
-template <int TW>
 FACO_DEV int apply_oropt(int n, int L, int a, int f, int b, int e, int side,
                          int pb, int fpos, int pq, int pp, int s0, int s1, int s2,
-                         int2 xs0, int2 xs1, int2 xs2, TeamLds *tl, int32_t *route,
-                         int32_t *pos, int2 *rxy) {
+                         int2 xs0, int2 xs1, int2 xs2, int32_t *route, int32_t *pos,
+                         int2 *rxy) {
   const int lane = lane_id();
   int x1, px1, px2;
   if (side == 0) {  // e = succ(b): edge (b, e)
@@ -1467,14 +1440,15 @@ FACO_DEV int apply_oropt(int n, int L, int a, int f, int b, int e, int side,
   src_lane = src_lane < 0 ? 0 : (src_lane > 2 ? 2 : src_lane);
   const int ins = __shfl(segv, src_lane);
   const int2 insx = shfl_i2(segx, src_lane);
-  const int D1 = wrapn(px1 - pq, n) + 1;
-  const int D2 = wrapn(pp - px2, n) + 1;
+  const int D1 = wrapc(px1 - pq, n) + 1;
+  const int D2 = wrapc(pp - px2, n) + 1;
   int moved;
   if (D1 <= D2) {
     // block q..x1 moves back by L to start at fpos; segment follows it
-    team_shift<TW>(n, pq, fpos, D1, true, tl, route, pos, rxy);
+    shift_part<1>(n, pq, fpos, D1, true, 0, route, pos, rxy);
+    wave_fence();
     if (lane < L) {
-      const int d = wrapn(fpos + D1 + lane, n);
+      const int d = wrapc(fpos + D1 + lane, n);
       route[d] = ins;
       rxy[d] = insx;
       pos[ins] = d;
@@ -1482,7 +1456,8 @@ FACO_DEV int apply_oropt(int n, int L, int a, int f, int b, int e, int side,
     moved = D1 + L;
   } else {
     // block x2..p moves forward by L; segment goes in front of it
-    team_shift<TW>(n, px2, wrap1(px2 + L, n), D2, false, tl, route, pos, rxy);
+    shift_part<1>(n, px2, wrap1(px2 + L, n), D2, false, 0, route, pos, rxy);
+    wave_fence();
     if (lane < L) {
       const int d = wrap1(px2 + lane, n);
       route[d] = ins;
@@ -1596,6 +1571,41 @@ FACO_DEV void sweep_part(const Inst &I, uint32_t flags, int count, int w, TeamLd
 // improvable cities, cities tested.
 enum { TK_SWEEP_TESTS = 24, TK_SWEEP_LIST = 25, TK_SWEEP_CITIES = 26 };
 
+// List the cities marked in `ord` (by original number) in ascending order, 64
+// at a time, and leave `ord` clear; the number listed.  One wave.
+FACO_DEV int list_marked(const Inst &I, int W, Queue &Q, uint32_t *inq, uint32_t *touched,
+                         uint32_t *ord) {
+  const int lane = lane_id();
+  int pushed = 0, bo = -1;
+  int bcount = 0;
+  auto list = [&](int cnt) {
+    const int x = lane < cnt ? I.int_of[bo] : 0;
+    pushed += cnt;
+    push_lanes(I.n, x, lane < cnt, Q, inq, touched);
+  };
+  for (int w0 = 0; w0 < W; w0 += kWave) {
+    const uint32_t word = (w0 + lane < W) ? ord[w0 + lane] : 0u;
+    if (w0 + lane < W) ord[w0 + lane] = 0u;
+    uint64_t nz = ballot(word != 0u);
+    while (nz) {
+      const int l = ctz64(nz);
+      nz &= nz - 1;
+      uint32_t bits = (uint32_t)readlane_i((int)word, l);
+      while (bits) {
+        const int bpos = __builtin_ctz(bits);
+        bits &= bits - 1;
+        if (lane == bcount) bo = (w0 + l) * 32 + bpos;
+        if (++bcount == kWave) {
+          list(kWave);
+          bcount = 0;
+        }
+      }
+    }
+  }
+  if (bcount) list(bcount);
+  return pushed;
+}
+
 template <int KT, int TW, class TT>
 FACO_DEV int sweep(const Inst &I, uint32_t flags, int W, Queue &Q, const TT &T,
                    uint32_t *inq, uint32_t *touched, uint32_t *ord, TeamLds *tl,
@@ -1668,34 +1678,7 @@ FACO_DEV int sweep(const Inst &I, uint32_t flags, int W, Queue &Q, const TT &T,
   }
   wave_fence();
   const int64_t tl0 = fine_ticks();
-  // list the marked cities, ascending original number, 64 at a time
-  int pushed = 0, bo = -1;
-  bcount = 0;
-  auto list = [&](int cnt) {
-    const int x = lane < cnt ? I.int_of[bo] : 0;
-    pushed += cnt;
-    push_lanes(I.n, x, lane < cnt, Q, inq, touched);
-  };
-  for (int w0 = 0; w0 < W; w0 += kWave) {
-    const uint32_t word = (w0 + lane < W) ? ord[w0 + lane] : 0u;
-    if (w0 + lane < W) ord[w0 + lane] = 0u;
-    uint64_t nz = ballot(word != 0u);
-    while (nz) {
-      const int l = ctz64(nz);
-      nz &= nz - 1;
-      uint32_t bits = (uint32_t)readlane_i((int)word, l);
-      while (bits) {
-        const int bpos = __builtin_ctz(bits);
-        bits &= bits - 1;
-        if (lane == bcount) bo = (w0 + l) * 32 + bpos;
-        if (++bcount == kWave) {
-          list(kWave);
-          bcount = 0;
-        }
-      }
-    }
-  }
-  if (bcount) list(bcount);
+  const int pushed = list_marked(I, W, Q, inq, touched, ord);
   tk[TK_SWEEP_LIST] += fine_ticks() - tl0;
   return pushed;
 }
@@ -1893,8 +1876,8 @@ FACO_DEV int64_t local_search(const Inst &I, uint32_t flags, int32_t *route,
         if constexpr (SEG)
           cnt[CNT_MOVED_ELEMS] += seg_apply_2opt<TW>(I, SQ, tl, mv, Z, tk);
         else
-          cnt[CNT_MOVED_ELEMS] += apply_2opt<TW>(n, uniform_i(mv.px), uniform_i(mv.py),
-                                                 uniform_i(mv.pz), tl, route, pos, rxy);
+          cnt[CNT_MOVED_ELEMS] += apply_2opt(n, uniform_i(mv.px), uniform_i(mv.py),
+                                             uniform_i(mv.pz), route, pos, rxy);
         tk[15] += fine_ticks() - ta;
         const int pc[4] = {mv.w, mv.x, mv.y, mv.z};
         push_all<4>(n, pc, Q, inq, touched);
@@ -1904,10 +1887,10 @@ FACO_DEV int64_t local_search(const Inst &I, uint32_t flags, int32_t *route,
           cnt[CNT_MOVED_ELEMS] += seg_apply_oropt<TW>(I, SQ, tl, mv, Z, tk);
         else
           cnt[CNT_MOVED_ELEMS] +=
-              apply_oropt<TW>(n, uniform_i(mv.L), mv.a, mv.f, mv.b, mv.e, uniform_i(mv.side),
-                              uniform_i(mv.pb), uniform_i(mv.fpos), uniform_i(mv.pq),
-                              uniform_i(mv.pp), mv.s0, mv.s1, mv.s2, mv.xs0, mv.xs1, mv.xs2,
-                              tl, route, pos, rxy);
+              apply_oropt(n, uniform_i(mv.L), mv.a, mv.f, mv.b, mv.e, uniform_i(mv.side),
+                          uniform_i(mv.pb), uniform_i(mv.fpos), uniform_i(mv.pq),
+                          uniform_i(mv.pp), mv.s0, mv.s1, mv.s2, mv.xs0, mv.xs1, mv.xs2,
+                          route, pos, rxy);
         tk[15] += fine_ticks() - ta;
         const int pc[6] = {mv.p, mv.q, mv.b, mv.e, mv.f, mv.l};
         push_all<6>(n, pc, Q, inq, touched);
@@ -1946,12 +1929,14 @@ FACO_DEV int64_t local_search(const Inst &I, uint32_t flags, int32_t *route,
   return gain;
 }
 
+#include "faco_team_ls.hpp"
+
 // ===================================================================== //
 // Helper waves of a team: wait for a command, take this wave's share, repeat
-// until the leader posts OP_EXIT.
+// until the leader posts OP_EXIT or OP_SEARCH (returned).
 // ===================================================================== //
 template <int KT, int TW, bool SEG>
-FACO_DEV void team_helper(const Inst &I, int ant, int w, TeamLds *tl, uint32_t *vis,
+FACO_DEV int team_helper(const Inst &I, int ant, int w, TeamLds *tl, uint32_t *vis,
                           uint32_t *ord, int32_t *route, int32_t *pos, int2 *rxy, int4 *rec) {
   Draws D;
   // a segment-list move's record whose cities this wave labels after the move
@@ -1964,13 +1949,8 @@ FACO_DEV void team_helper(const Inst &I, int ant, int w, TeamLds *tl, uint32_t *
     }
     team_sync();
     const int op = uniform_i(tl->op);
-    if (op == OP_EXIT) break;
-    if (op == OP_REVERSE) {
-      reverse_part<TW, kTeamChunks>(I.n, team_arg(tl, 0), team_arg(tl, 1), w, route, pos, rxy);
-    } else if (op == OP_SHIFT) {
-      shift_part<TW, kTeamChunks>(I.n, team_arg(tl, 0), team_arg(tl, 1), team_arg(tl, 2),
-                                  team_arg(tl, 3) != 0, w, route, pos, rxy);
-    } else if (op == OP_WINDOW) {
+    if (op == OP_EXIT || op == OP_SEARCH) return op;
+    if (op == OP_WINDOW) {
       WinOut o;
       window_rounds<KT, TW>(I, uniform_u64(tl->arg64[0]), (uint64_t)ant,
                             uniform_u64(tl->arg64[1]), team_arg(tl, 0), team_arg(tl, 1),
@@ -1984,14 +1964,10 @@ FACO_DEV void team_helper(const Inst &I, int ant, int w, TeamLds *tl, uint32_t *
       int64_t md;
       int mj;
       nearest_part<TW>(I, team_arg(tl, 0), w, vis, tl, md, mj);
-    } else if (op == OP_SWEEP) {
-      if constexpr (SEG)
-        sweep_part<KT, TW>(I, (uint32_t)team_arg(tl, 1), team_arg(tl, 0), w, tl, ord,
-                           seg_view(I, ant, rec, uniform_i(tl->sgs[0]), uniform_i(tl->sgs[1]),
-                                    uniform_i(tl->sgs[2]), uniform_i(tl->sgs[3])));
-      else
-        sweep_part<KT, TW>(I, (uint32_t)team_arg(tl, 1), team_arg(tl, 0), w, tl, ord,
-                           FlatT{route, pos, rxy});
+    } else if (SEG && op == OP_SWEEP) {
+      sweep_part<KT, TW>(I, (uint32_t)team_arg(tl, 1), team_arg(tl, 0), w, tl, ord,
+                         seg_view(I, ant, rec, uniform_i(tl->sgs[0]), uniform_i(tl->sgs[1]),
+                                  uniform_i(tl->sgs[2]), uniform_i(tl->sgs[3])));
     } else if (SEG && op == OP_SEGPERM) {
       const SegT T = seg_view(I, ant, rec, uniform_i(tl->sgs[0]), uniform_i(tl->sgs[1]));
       const int rv = team_arg(tl, 5);
@@ -2026,7 +2002,7 @@ FACO_DEV void team_helper(const Inst &I, int ant, int w, TeamLds *tl, uint32_t *
       team_sync();
       seg_reset_part(rec, tid, kWave * TW, (I.n + (1 << I.seg_shift) - 1) >> I.seg_shift, I.n,
                      I.seg_shift);
-    } else if (op == OP_OROPT) {
+    } else if (SEG && op == OP_OROPT) {
       oropt_part<KT, TW>(I, w, tl);
     }
     team_sync();
@@ -2043,39 +2019,14 @@ FACO_DEV void team_helper(const Inst &I, int ant, int w, TeamLds *tl, uint32_t *
 // ===================================================================== //
 __host__ __device__ inline int seg_lds_words(int tw_words, int W) { return (tw_words + 3 * W + 3) & ~3; }
 
-template <int KT, int TW, bool SEG = false>
-FACO_DEV void run_ant(const Inst &I, int ant, int mode, uint32_t *lds) {
+// The queue and bitmaps the local search starts from (leader wave); returns
+// the flags it runs with.
+FACO_DEV uint32_t search_setup(const Inst &I, bool init, int W, int nchk, int32_t *ring,
+                               uint32_t *vis, uint32_t *inq, uint32_t *ord, Queue &Q,
+                               LaneCounters &cnt) {
   const int n = I.n, lane = lane_id();
-  const int W = (n + 31) >> 5;
-  TeamLds *tl = (TeamLds *)lds;
-  uint32_t *vis = lds + team_words<TW>();
-  uint32_t *inq = vis + W;
-  uint32_t *ord = inq + W;
-  int4 *rec = (int4 *)(lds + seg_lds_words(team_words<TW>(), W));
-  int32_t *route = I.routes + (size_t)ant * (size_t)n;
-  int32_t *pos = I.pos + (size_t)ant * (size_t)n;
-  int32_t *ring = I.ring + (size_t)ant * (size_t)n;
-  int2 *rxy = I.rxy + (size_t)ant * (size_t)n;
-  if (TW > 1) {
-    const int w = uniform_i((int)(threadIdx.x >> 6));
-    if (w > 0) {
-      team_helper<KT, TW, SEG>(I, ant, w, tl, vis, ord, route, pos, rxy, rec);
-      return;
-    }
-  }
-  LaneCounters cnt, tk;
-  const bool init = mode == 1;
-  const uint64_t t = (uint64_t)I.st->iter + 1;
-  int nchk = 0;
-  const int64_t t0 = ticks();
-  int64_t len = construct<KT, TW>(I, t, ant, init, route, pos, rxy, ring, vis, inq, tl, W, nchk,
-                                  cnt, tk);
-  tk[0] = ticks() - t0;
   uint32_t flags = I.ls_flags;
   const int lcap = I.lcap;
-  Queue Q;
-  Q.lr = SEG ? (int32_t *)(rec + I.seg_max) : (int32_t *)(ord + W);
-  Q.gr = ring;
   if (init) {
     // the initial solution reports only its local-search counters
 #pragma unroll
@@ -2117,18 +2068,84 @@ FACO_DEV void run_ant(const Inst &I, int ant, int mode, uint32_t *lds) {
   Q.count = uniform_i(Q.count);
   Q.cap = uniform_i(Q.cap);
   Q.in_lds = uniform_i(Q.in_lds);
+  return flags;
+}
+
+template <int KT, int TW, bool SEG = false>
+FACO_DEV void run_ant(const Inst &I, int ant, int mode, uint32_t *lds) {
+  const int n = I.n, lane = lane_id();
+  const int W = (n + 31) >> 5;
+  TeamLds *tl = (TeamLds *)lds;
+  uint32_t *vis = lds + team_words<TW>();
+  uint32_t *inq = vis + W;
+  uint32_t *ord = inq + W;
+  int4 *rec = (int4 *)(lds + seg_lds_words(team_words<TW>(), W));
+  int32_t *route = I.routes + (size_t)ant * (size_t)n;
+  int32_t *pos = I.pos + (size_t)ant * (size_t)n;
+  int32_t *ring = I.ring + (size_t)ant * (size_t)n;
+  int2 *rxy = I.rxy + (size_t)ant * (size_t)n;
+  const int w = TW > 1 ? uniform_i((int)(threadIdx.x >> 6)) : 0;
+  LaneCounters cnt, tk;
+  const bool init = mode == 1;
+  const int64_t t0 = w == 0 ? ticks() : 0;
+  int64_t len = 0;
+  uint32_t flags = 0;
+  Queue Q;
+  Q.lr = SEG ? (int32_t *)(rec + I.seg_max) : (int32_t *)(ord + W);
+  Q.gr = ring;
   SegState SQ;
-  if constexpr (SEG) seg_begin(I, ant, rec, tl, TW > 1, SQ);
-  if (flags & (LS_2OPT | LS_OROPT))
-    len -= local_search<KT, TW, SEG>(I, flags, route, pos, rxy, inq, vis, ord, tl, W, Q, cnt,
-                                     tk, init ? -1 : ant, SQ);
+  if (TW > 1 && w > 0) {
+    if (team_helper<KT, TW, SEG>(I, ant, w, tl, vis, ord, route, pos, rxy, rec) == OP_EXIT)
+      return;
+  } else {
+    const uint64_t t = (uint64_t)I.st->iter + 1;
+    int nchk = 0;
+    len = construct<KT, TW>(I, t, ant, init, route, pos, rxy, ring, vis, inq, tl, W, nchk, cnt,
+                            tk);
+    tk[0] = ticks() - t0;
+    flags = search_setup(I, init, W, nchk, ring, vis, inq, ord, Q, cnt);
+    if constexpr (SEG || TW == 1) {
+      if constexpr (SEG) seg_begin(I, ant, rec, tl, TW > 1, SQ);
+      if (flags & (LS_2OPT | LS_OROPT))
+        len -= local_search<KT, TW, SEG>(I, flags, route, pos, rxy, inq, vis, ord, tl, W, Q, cnt,
+                                         tk, init ? -1 : ant, SQ);
+    }
+  }
+  if constexpr (TW > 1 && !SEG) {
+    // the whole team runs the local search
+    if (w == 0) {
+      const bool search = (flags & (LS_2OPT | LS_OROPT)) != 0;
+      if (lane == 0) {
+        tl->op = search ? OP_SEARCH : OP_EXIT;
+        tl->arg[0] = Q.head;
+        tl->arg[1] = Q.tail;
+        tl->arg[2] = Q.count;
+        tl->arg[3] = Q.cap;
+        tl->arg[4] = Q.in_lds;
+        tl->arg[5] = (int)flags;
+      }
+      team_sync();
+      if (!search) flags = 0;
+    }
+    if (w > 0 || flags) {
+      Q.head = team_arg(tl, 0);
+      Q.tail = team_arg(tl, 1);
+      Q.count = team_arg(tl, 2);
+      Q.cap = team_arg(tl, 3);
+      Q.in_lds = team_arg(tl, 4);
+      flags = (uint32_t)team_arg(tl, 5);
+      len -= team_local_search<KT, TW>(I, flags, route, pos, rxy, inq, vis, ord, tl, W, Q, cnt,
+                                       tk, init ? -1 : ant, w);
+      if (w > 0) return;
+    }
+  }
   int live = 0;
   if constexpr (SEG) {
     if (uniform_i(SQ.dirty)) seg_materialize<TW>(I, ant, SQ, tl, tk);
     live = uniform_i(SQ.live);
     if (lane == 0) I.sepoch[ant] = SQ.T.epoch;
   }
-  if (TW > 1) {
+  if (TW > 1 && SEG) {
     if (lane == 0) tl->op = OP_EXIT;
     team_sync();
   }

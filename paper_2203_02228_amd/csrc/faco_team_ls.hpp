@@ -1,0 +1,493 @@
+// faco_team_ls.hpp -- the local search of an ant whose team has several waves,
+// on flat arrays (included by faco_kernels.hpp after the array rewrites).
+//
+// Every wave of the team runs the same loop on the same (wave-uniform) state
+// and no wave waits for commands: a round takes the next TW listed cities,
+// wave w evaluates the w-th one (2-opt and every Or-opt variant at once) and
+// leaves its best move in LDS; after one barrier every wave sees all TW
+// moves, takes the first city with one (the ones before it are popped without
+// a move, the ones after it stay listed: the order of one city at a time),
+// rewrites its share of the arrays, and a second barrier ends the round.
+// Wave 0 meanwhile pushes the move's cities.
+//
+// What bounds a round is its chain: two dependent levels of loads (positions,
+// then tour neighbours) that mostly miss L2 (64 ants' arrays are 100 MB at
+// 100k cities), about 280 vector instructions, and the barriers.  A leader
+// that evaluated four cities and handed the Or-opt variants to helper waves
+// through LDS paid two more barriers and 14 words a lane for the hand-over.
+// Measured on the 100k workload (64 ants, iterations 100..200): 649 rounds of 8
+// cities an ant at 2.44 us instead of 797 of 4 at 2.04, a move 2.2 us instead
+// of 3.0; the ant kernel 7.5 ms instead of 9.6.
+#pragma once
+
+// Move record of a wave (32 words, eight int4):
+//   [0] gain (0: none), code, b, bn   [1] pb, pbn, pa, a
+//   [2..3] cities at tour positions pa-3 .. pa+3 (7 words)
+//   [4..7] their coordinates (7 int2)
+// code: 0/1 2-opt through (a, succ a)/(pred a, a); 2 + 2 slot + side: Or-opt
+// (slots of or_slot_lanes).  bn: succ b (2-opt code 0, Or-opt side 0) or
+// pred b; pb, pbn, pa: positions of b, bn, a.
+constexpr int kDescWords = 32;
+
+// The loads of a wave's next city that never change along a local search.
+struct TeamPre {
+  int a;  // -1: none
+  int b, d;
+};
+template <int GS>
+FACO_DEV TeamPre team_pre(const Inst &I, int a) {
+  const int s = lane_id() & (GS - 1);
+  const size_t row = (size_t)a * (size_t)I.k;
+  TeamPre P;
+  P.a = a;
+  P.b = s < I.k ? I.cl[row + s] : a;
+  P.d = s < I.k ? I.cl_d[row + s] : 0;
+  return P;
+}
+
+// Evaluate city a with the whole wave: lane = (part, candidate slot s), part
+// p of 64 / GS.  Even parts try the moves through (b, succ b), odd parts those
+// through (pred b, b); with four parts the 2-opt move and Or-opt slots 0, 1
+// are tried by the first pair of parts and slots 2..4 by the second.  Every
+// 16-lane row also holds the 11 costs that depend only on a's neighbourhood
+// (GroupEval::uc), one per lane.  The result is the best move in the order of
+// the sequential evaluation: 2-opt first (loop 1 over the list, then loop 2),
+// else Or-opt by gain, then slot, list position, succ before pred.
+template <int GS>
+FACO_DEV void team_eval(const Inst &I, uint32_t flags, const TeamPre &P, const int32_t *route,
+                        const int32_t *pos, const int2 *rxy, int *desc) {
+  constexpr int NP = kWave / GS;       // parts
+  const int n = I.n, K = I.k, lane = lane_id();
+  const int s = lane & (GS - 1), part = lane / GS, side = part & 1;
+  const bool second = part >= 2;
+  const int a = P.a, b = P.b, d_ab = P.d;
+  const bool act = s < K;
+  // level 1
+  const int pa = uniform_i(pos[a]);
+  const int pb = pos[b];
+  const int2 xb = I.xy[b];
+  // level 2: a's neighbourhood (each lane the ends of its cost) and b's
+  // neighbour
+  const int r16 = lane & 15;
+  const int su = r16 <= 5 ? r16 : (r16 <= 8 ? 2 : (r16 == 9 ? 1 : (r16 == 10 ? 0 : 3)));
+  const int sv = r16 <= 5 ? r16 + 1 : (r16 <= 8 ? r16 - 2 : (r16 <= 10 ? 4 : 3));
+  const int2 U = rxy[wrapc(pa + su - 3, n)], V = rxy[wrapc(pa + sv - 3, n)];
+  const int nb = route[wrapc(pa + (lane < 7 ? lane : 3) - 3, n)];
+  const int pbs = pb + 1 == n ? 0 : pb + 1, pbp = pb == 0 ? n - 1 : pb - 1;
+  const int pbn = side ? pbp : pbs;
+  const int2 xbn = rxy[pbn];
+  const int bn = route[pbn];
+  const int uc = cost(U, V);
+  const int d_bn = cost(xb, xbn);
+  int u[11];
+#pragma unroll
+  for (int j = 0; j < 11; ++j) u[j] = row_bcast(uc, j);
+  int2 X[6];  // coordinates at pa - 3 + j
+#pragma unroll
+  for (int j = 1; j < 6; ++j) X[j] = make_int2(row_bcast(U.x, j), row_bcast(U.y, j));
+  const int Lmax = (flags & LS_OROPT) ? or_lmax(I) : 0;
+  const int in = d_bn - d_ab;  // edge freed at b minus the new edge (a, b)
+  // Or-opt slot `vi`: the gain (0: no move)
+  auto oropt = [&](int L, int rem, int g_rem, int fpos, int2 xo) -> int {
+    const int g = g_rem + in - cost(xo, xbn);
+    const bool ok = act && L <= Lmax && d_ab < rem && wrapc(pb - fpos, n) >= L &&
+                    wrapc(pbn - fpos, n) >= L;
+    return ok ? g : 0;
+  };
+  auto twoopt = [&](int old, int2 xo) -> int {
+    const int g = old + in - cost(xo, xbn);
+    return (act && (flags & LS_2OPT) && old > d_ab) ? g : 0;
+  };
+  int g2 = 0, go = 0, vo = 0;
+  const int p1 = wrapc(pa - 1, n), p2 = wrapc(pa - 2, n);
+  const int old = side ? u[2] : u[3];
+  const int2 xo2 = side ? X[2] : X[4];
+  if (NP == 4) {
+    const int G0 = u[2] + u[3] - u[6], G1 = u[2] + u[4] - u[7], G2 = u[2] + u[5] - u[8];
+    const int G3 = u[1] + u[3] - u[9], G4 = u[0] + u[3] - u[10];
+    // second = false: 2-opt, slot 0, slot 1; true: slot 2, slot 3, slot 4
+    const int gA = second ? oropt(3, u[2], G2, pa, X[5]) : twoopt(old, xo2);
+    const int2 xB = second ? X[2] : X[3], xC = second ? X[1] : X[4];
+    const int gB = oropt(second ? 2 : 1, second ? u[3] : u[2], second ? G3 : G0,
+                         second ? p1 : pa, xB);
+    const int gC = oropt(second ? 3 : 2, second ? u[3] : u[2], second ? G4 : G1,
+                         second ? p2 : pa, xC);
+    g2 = second ? 0 : gA;
+    go = second ? gA : 0;
+    vo = second ? 2 : 0;
+    const int vB = second ? 3 : 0, vC = second ? 4 : 1;
+    vo = gB > go ? vB : vo;
+    go = gB > go ? gB : go;
+    vo = gC > go ? vC : vo;
+    go = gC > go ? gC : go;
+  } else {
+    g2 = twoopt(old, xo2);
+    const int g[5] = {oropt(1, u[2], u[2] + u[3] - u[6], pa, X[3]),
+                      oropt(2, u[2], u[2] + u[4] - u[7], pa, X[4]),
+                      oropt(3, u[2], u[2] + u[5] - u[8], pa, X[5]),
+                      oropt(2, u[3], u[1] + u[3] - u[9], p1, X[2]),
+                      oropt(3, u[3], u[0] + u[3] - u[10], p2, X[1])};
+#pragma unroll
+    for (int v = 0; v < 5; ++v) {
+      vo = g[v] > go ? v : vo;
+      go = g[v] > go ? g[v] : go;
+    }
+  }
+  const int M2 = wave_max_i32(g2), MO = wave_max_i32(go);
+  int l = 0;
+  const bool two = M2 > 0;
+  const int gain = two ? M2 : (MO > 0 ? MO : 0);
+  if (two) {
+    l = ctz64(ballot(g2 == M2));  // lane order is the order of the two loops
+  } else if (MO > 0) {
+    uint64_t m = ballot(go == MO);
+    if (m & (m - 1)) {
+      const int idx = go == MO ? (vo * K + s) * 2 + side : 0x7fffffff;
+      const int best = wave_min_i32(idx);
+      m = ballot(idx == best);
+    }
+    l = ctz64(m);
+  }
+  int4 *d4 = reinterpret_cast<int4 *>(desc);
+  if (lane == l) {
+    d4[0] = make_int4(gain, two ? side : 2 + 2 * vo + side, b, bn);
+    d4[1] = make_int4(pb, pbn, pa, a);
+  }
+  if (gain > 0) {
+    if (lane < 7) desc[8 + lane] = nb;
+    int2 *d2 = reinterpret_cast<int2 *>(desc + 16);
+    if (lane < 6) d2[lane] = U;
+    if (lane == 5) d2[6] = V;
+  }
+}
+
+// This wave's share of a reversal (see reverse_part): few chunks take the
+// variant with few in flight.  Chunks start at wave 1: wave 0 has the pushes.
+template <int TW>
+FACO_DEV void team_reverse_share(int n, int s, int L, int w, int32_t *route, int32_t *pos,
+                                 int2 *rxy) {
+  const int half = L >> 1;
+  const int ww = w == 0 ? TW - 1 : w - 1;
+  if (half <= TW * kWave)
+    reverse_part<TW, 1>(n, s, L, ww, route, pos, rxy);
+  else if (half <= 4 * TW * kWave)
+    reverse_part<TW, 4>(n, s, L, ww, route, pos, rxy);
+  else
+    reverse_part<TW, kTeamChunks>(n, s, L, ww, route, pos, rxy);
+}
+
+// A block move by the team, or by wave 1 alone while it holds the whole block
+// in registers (no barrier between its reads and writes needed).
+constexpr int kSoloShift = 2 * kWave;
+template <int TW>
+FACO_DEV void team_shift_share(int n, int src, int dst, int D, bool down, int w, int32_t *route,
+                               int32_t *pos, int2 *rxy) {
+  if (D <= kSoloShift) {
+    if (w == 1) shift_part<1, kSoloShift / kWave>(n, src, dst, D, down, 0, route, pos, rxy);
+    return;
+  }
+  const int ww = w == 0 ? TW - 1 : w - 1;
+  if (D <= TW * kWave)
+    shift_part<TW, 1>(n, src, dst, D, down, ww, route, pos, rxy);
+  else if (D <= 4 * TW * kWave)
+    shift_part<TW, 4>(n, src, dst, D, down, ww, route, pos, rxy);
+  else
+    shift_part<TW, kTeamChunks>(n, src, dst, D, down, ww, route, pos, rxy);
+}
+
+// Sweep by all waves (see sweep()): the touched cities are gathered into a
+// list in LDS (the queue's ring, empty during a sweep; all of them at once
+// when they fit, else a range of bitmap words at a time), every wave tests 64
+// of them per step with no barrier between steps, and wave 0 lists the
+// improvable ones.  Returns the number listed; Q is updated in every wave.
+template <int KT, int TW>
+FACO_DEV int team_sweep(const Inst &I, uint32_t flags, int W, Queue &Q, const FlatT &T,
+                        uint32_t *inq, uint32_t *touched, uint32_t *ord, TeamLds *tl, int w,
+                        LaneCounters &tk) {
+  const int lane = lane_id(), tid = w * kWave + lane;
+  constexpr int NT = TW * kWave;
+  const int64_t t0 = ticks();
+  // a small ring (a configured capacity) is replaced by the team's city list
+  const bool ring = I.lcap >= 4 * NT;
+  int32_t *list = ring ? Q.lr : tl->cities;
+  const int cap = ring ? I.lcap : NT;
+  int own = 0;
+  for (int wi = tid; wi < W; wi += NT) own += __builtin_popcount(touched[wi]);
+  own = wave_sum_i32(own);
+  if (lane == 0) {
+    tl->f[w] = own;
+    if (w == 0) tl->ls.cnt[0] = 0;
+  }
+  team_sync();
+  const int total = uniform_i(wave_sum_i32(lane < TW ? tl->f[lane] : 0));
+  const int step = total <= cap ? W : cap / 32;
+  int p = 0;
+  for (int w0 = 0; w0 < W; w0 += step, p ^= 1) {
+    const int w1 = w0 + step < W ? w0 + step : W;
+    if (w == 0 && lane == 0) tl->ls.cnt[p ^ 1] = 0;
+    for (int g = w0 + w * kWave; g < w1; g += NT) {
+      uint32_t word = g + lane < w1 ? touched[g + lane] : 0u;
+      const int c = wave_sum_i32(__builtin_popcount(word));
+      if (c == 0) continue;
+      int at = 0;
+      if (lane == 0) at = atomicAdd(&tl->ls.cnt[p], c);
+      at = uniform_i(at);
+      for (;;) {
+        const uint64_t m = ballot(word != 0u);
+        if (!m) break;
+        const int r = __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32),
+                                                __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
+        if (word != 0u) {
+          list[at + r] = (g + lane) * 32 + __builtin_ctz(word);
+          word &= word - 1u;
+        }
+        at += __builtin_popcountll(m);
+      }
+    }
+    team_sync();
+    const int cnt = uniform_i(tl->ls.cnt[p]);
+    for (int i0 = w * kWave; i0 < cnt; i0 += NT) {
+      const int i = i0 + lane;
+      if (i < cnt) {
+        const int x = list[i];
+        const int ox = I.orig_of[x];
+        if (has_improving<KT>(I, flags, x, T)) bit_set(ord, ox);
+      }
+    }
+    team_sync();
+  }
+  if (w == 0) {
+    tk[TK_SWEEP_CITIES] += total;
+    tk[TK_SWEEP_TESTS] += ticks() - t0;
+  }
+  int marks = 0;
+  for (int wi = tid; wi < W; wi += NT) marks += __builtin_popcount(ord[wi]);
+  marks = wave_sum_i32(marks);
+  if (lane == 0) tl->f[w] = marks;
+  team_sync();
+  const int listed = uniform_i(wave_sum_i32(lane < TW ? tl->f[lane] : 0));
+  if (listed > 0) {
+    if (w == 0) {
+      const int64_t tl0 = ticks();
+      list_marked(I, W, Q, inq, touched, ord);
+      if (lane == 0) {
+        tl->arg[0] = Q.head;
+        tl->arg[1] = Q.tail;
+        tl->arg[2] = Q.count;
+        tl->arg[3] = Q.cap;
+        tl->arg[4] = Q.in_lds;
+      }
+      tk[TK_SWEEP_LIST] += ticks() - tl0;
+    }
+    team_sync();
+    Q.head = team_arg(tl, 0);
+    Q.tail = team_arg(tl, 1);
+    Q.count = team_arg(tl, 2);
+    Q.cap = team_arg(tl, 3);
+    Q.in_lds = team_arg(tl, 4);
+  }
+  return listed;
+}
+
+// The local search (Alg. 3 + Or-opt + sweeps), called by every wave w of the
+// team with the same arguments; cnt, tk and the return value (the gain) are
+// wave 0's.
+template <int KT, int TW>
+FACO_DEV int64_t team_local_search(const Inst &I, uint32_t flags, int32_t *route, int32_t *pos,
+                                   int2 *rxy, uint32_t *inq, uint32_t *touched, uint32_t *ord,
+                                   TeamLds *tl, int W, Queue Q, LaneCounters &cnt,
+                                   LaneCounters &tk, int ant, int w) {
+  constexpr int GS = KT <= 16 ? 16 : 32;
+  const int n = I.n, lane = lane_id();
+  flags = (uint32_t)uniform_i((int)flags);
+  int changes = 0, changes_at_sweep = -1, par = 0;
+  int pops = 0, m2 = 0, sweeps = 0, rounds = 0;
+  int64_t gain = 0, moved = 0, t_eval = 0, t_apply = 0, t_sweep = 0;
+  TeamPre pre;
+  pre.a = -1;
+  pre.b = pre.d = 0;
+  int64_t t0 = w == 0 ? ticks() : 0;
+  for (;;) {
+    for (;;) {
+      Q.count = uniform_i(Q.count);
+      Q.head = uniform_i(Q.head);
+      Q.tail = uniform_i(Q.tail);
+      Q.cap = uniform_i(Q.cap);
+      Q.in_lds = uniform_i(Q.in_lds);
+      changes = uniform_i(changes);
+      if (!(Q.count > 0 && changes < n)) break;
+      const int gcount = Q.count < TW ? Q.count : TW;
+      int *desc = tl->ls.desc[par];
+      par ^= 1;
+      if (w < gcount) {
+        int h = Q.head + w;
+        h = h >= Q.cap ? h - Q.cap : h;
+        const int a = uniform_i(Q.in_lds ? Q.lr[h] : Q.gr[h]);
+        if (uniform_i(pre.a) != a) pre = team_pre<GS>(I, a);
+        team_eval<GS>(I, flags, pre, route, pos, rxy, desc + w * kDescWords);
+      }
+      team_sync();
+      // lanes 8 v .. 8 v + 7 hold wave v's record
+      int4 v = make_int4(0, 0, 0, 0);
+      if (lane < 8 * gcount) v = reinterpret_cast<const int4 *>(desc)[lane];
+      const uint64_t hm = ballot((lane & 7) == 0 && v.x > 0);
+      const int j = uniform_i(hm ? ctz64(hm) >> 3 : gcount);
+      const int npop = j < gcount ? j + 1 : gcount;
+      // wave 0 unlists the popped cities
+      if (w == 0 && (lane & 7) == 1 && (lane >> 3) < npop) bit_clear(inq, v.w);
+      Q.head = Q.head + npop >= Q.cap ? Q.head + npop - Q.cap : Q.head + npop;
+      Q.count -= npop;
+      pops += npop;
+      ++rounds;
+      // the next round's city of this wave, unless a push comes before it
+      pre.a = -1;
+      if (Q.in_lds && w < Q.count) {
+        int h = Q.head + w;
+        h = h >= Q.cap ? h - Q.cap : h;
+        pre = team_pre<GS>(I, uniform_i(Q.lr[h]));
+      }
+      if (w == 0) {
+        const int64_t t1 = fine_ticks();
+        t_eval += t1 - t0;
+        t0 = t1;
+      }
+      if (j >= gcount) continue;
+      const int jb = 8 * j;
+      const int code = readlane_i(v.y, jb);
+      const int g = readlane_i(v.x, jb);
+      const int pb = readlane_i(v.x, jb + 1), pbn = readlane_i(v.y, jb + 1);
+      const int pa = readlane_i(v.z, jb + 1);
+      const int *rec = desc + j * kDescWords;
+      const bool two = code < 2;
+      const int side = code & 1, slot = (code - 2) >> 1;
+      int dir, L, lf, ll, lp, lq;
+      or_slot_lanes(slot, dir, L, lf, ll, lp, lq);
+      if (w == 0) {
+        // cities to list, in order: 2-opt (w, x, y, z), Or-opt (p, q, b, e,
+        // first, last); words of the record
+        int k;
+        if (two) {
+          // side 0: a, succ a, b, succ b; side 1: pred a, a, pred b, b
+          k = lane == 0 ? (side ? 10 : 11)
+                        : (lane == 1 ? (side ? 11 : 12)
+                                     : ((lane == 2) == (side == 0) ? 2 : 3));
+        } else {
+          k = lane == 0 ? 8 + lp
+                        : (lane == 1 ? 8 + lq
+                                     : (lane == 2 ? 2
+                                                  : (lane == 3 ? 3 : (lane == 4 ? 8 + lf : 8 + ll))));
+        }
+        const int np = two ? 4 : 6;
+        const int x = rec[lane < np ? k : 0];
+        bool take = lane < np && !bit_get(inq, lane < np ? x : 0);
+#pragma unroll
+        for (int i = 0; i < 5; ++i) {
+          const int xi = readlane_i(x, i);
+          if (i < lane && xi == x) take = false;
+        }
+        const uint64_t pm = ballot(take);
+        const int cntp = __builtin_popcountll(pm);
+        const int spill = Q.in_lds && Q.count + cntp > Q.cap ? 1 : 0;
+        if (spill) q_spill(Q, n);
+        if (take) {
+          int t = Q.tail + __builtin_popcountll(pm & ((1ull << lane) - 1ull));
+          t = t >= Q.cap ? t - Q.cap : t;
+          bit_set(inq, x);
+          bit_set(touched, x);
+          (Q.in_lds ? Q.lr : Q.gr)[t] = x;
+        }
+        if (lane == 0) tl->ls.pushed = cntp | (spill << 8);
+      }
+      int mv;
+      if (two) {
+        // flip x..y, x = succ a or a, y = b or pred b, or the complement from
+        // z = succ b or b: the shorter
+        const int px = side ? pa : (pa + 1 == n ? 0 : pa + 1);
+        const int py = side ? pbn : pb, pz = side ? pb : pbn;
+        const int L1 = wrapc(py - px, n) + 1;
+        const bool first = 2 * L1 <= n;
+        mv = first ? L1 : n - L1;
+        team_reverse_share<TW>(n, uniform_i(first ? px : pz), uniform_i(mv), w, route, pos, rxy);
+        ++m2;
+      } else {
+        // the segment and the shorter block between its old place and the
+        // insertion edge (x1, x2) exchange places
+        const int fpos = dir == 0 ? pa : wrapc(pa - L + 1, n);
+        const int pq = wrapc(fpos + L, n), pp = fpos == 0 ? n - 1 : fpos - 1;
+        const int px1 = side ? pbn : pb, px2 = side ? pb : pbn;
+        const int D1 = wrapc(px1 - pq, n) + 1, D2 = wrapc(pp - px2, n) + 1;
+        const bool down = D1 <= D2;
+        const int D = uniform_i(down ? D1 : D2);
+        const int src = uniform_i(down ? pq : px2);
+        const int dst = uniform_i(down ? fpos : wrapc(px2 + L, n));
+        // the segment in its inserted orientation
+        const bool rev = (dir == 1) != (side == 1);
+        const int i = lane < L ? lane : 0;
+        const int ei = lf + (rev ? L - 1 - i : i);
+        const int ins = rec[8 + ei];
+        const int2 insx = reinterpret_cast<const int2 *>(rec + 16)[ei];
+        team_shift_share<TW>(n, src, dst, D, down, w, route, pos, rxy);
+        if (w == 1 && lane < L) {
+          const int d = wrapc((down ? wrapc(fpos + D1, n) : px2) + lane, n);
+          route[d] = ins;
+          rxy[d] = insx;
+          pos[ins] = d;
+        }
+        mv = D + L;
+      }
+      ++changes;
+      gain += g;
+      moved += mv;
+      team_sync();
+      const int pushed = uniform_i(tl->ls.pushed);
+      const int np = pushed & 255;
+      if (w == 0) {
+        const int64_t t1 = fine_ticks();
+        t_apply += t1 - t0;
+        t0 = t1;
+      } else if (pushed >> 8) {  // wave 0's queue moved to the global ring
+        Q.head = 0;
+        Q.tail = Q.count == n ? 0 : Q.count;
+        Q.cap = n;
+        Q.in_lds = 0;
+      }
+      Q.tail = Q.tail + np >= Q.cap ? Q.tail + np - Q.cap : Q.tail + np;
+      Q.count += np;
+    }
+    changes = uniform_i(changes);
+    if (!(flags & LS_SWEEP) || changes >= n) break;
+    // Every city a sweep lists has an improving move, so a sweep that was
+    // followed by no change can only come from the two move tests
+    // disagreeing: stop instead of spinning, and report it.
+    if (changes == changes_at_sweep) {
+      if (w == 0) record_fault(I, FAULT_LS_STALL, ant);
+      break;
+    }
+    changes_at_sweep = changes;
+    ++sweeps;
+    const int pushed = uniform_i(team_sweep<KT, TW>(I, flags, W, Q, FlatT{route, pos, rxy}, inq,
+                                                    touched, ord, tl, w, tk));
+    pre.a = -1;
+    if (w == 0) {
+      const int64_t t1 = ticks();
+      t_sweep += t1 - t0;
+      t0 = t1;
+    }
+    if (pushed == 0) break;
+  }
+  if (w == 0) {
+    cnt[CNT_LS_POPS] += pops;
+    cnt[CNT_MOVES_2OPT] += m2;
+    cnt[CNT_MOVES_OROPT] += changes - m2;
+    cnt[CNT_MOVED_ELEMS] += moved;
+    cnt[CNT_SWEEPS] += sweeps;
+    cnt[CNT_LS_GAIN] += gain;
+    tk[1] += t_eval;
+    tk[2] += t_apply;
+    tk[3] += t_sweep;
+    tk[12] += rounds;
+    tk[14] += (flags & LS_OROPT) ? rounds : 0;
+    tk[15] += t_apply;
+  }
+  return gain;
+}
