@@ -4,6 +4,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <type_traits>
+
 #define FACO_DEV __device__ __forceinline__
 
 namespace faco {
@@ -46,9 +48,12 @@ constexpr int kDppQuad2301 = 0x4E;
 constexpr int kDppRowHalfMirror = 0x141;
 constexpr int kDppRowMirror = 0x140;
 
+// Every lane's source lane exists for the controls used, so the bound_ctrl bit
+// changes nothing; with it set the compiler folds the move into the operation
+// that uses it.
 template <int CTRL>
 FACO_DEV int dpp_i(int v) {
-  return __builtin_amdgcn_mov_dpp(v, CTRL, 0xF, 0xF, false);
+  return __builtin_amdgcn_mov_dpp(v, CTRL, 0xF, 0xF, true);
 }
 template <int CTRL>
 FACO_DEV int64_t dpp_i64(int64_t v) {
@@ -112,7 +117,17 @@ FACO_DEV int64_t wave_min_i64(int64_t v) { return wave_reduce_i64(v, OpMin()); }
 FACO_DEV int64_t wave_sum_i64(int64_t v) { return wave_reduce_i64(v, OpAdd()); }
 FACO_DEV int wave_sum_i32(int v) { return wave_reduce_i32(v, OpAdd()); }
 FACO_DEV int wave_min_i32(int v) { return wave_reduce_i32(v, OpMin()); }
-FACO_DEV int wave_max_i32(int v) { return wave_reduce_i32(v, OpMax()); }
+// Maximum over the wave: rows by DPP, then lane 15 of rows 0 and 2 to the next
+// row and lane 31 to the upper half (DPP row broadcasts 15 and 31), which
+// leaves the whole wave's maximum in lane 63.
+FACO_DEV int wave_max_i32(int v) {
+  v = row_reduce_i32(v, OpMax());
+  int o = __builtin_amdgcn_update_dpp(v, v, 0x142, 0xA, 0xF, false);
+  v = o > v ? o : v;
+  o = __builtin_amdgcn_update_dpp(v, v, 0x143, 0xC, 0xF, false);
+  v = o > v ? o : v;
+  return readlane_i(v, 63);
+}
 
 // A value every lane holds alike, moved to a scalar register: control flow
 // on it is a scalar branch (needed where a workgroup barrier follows).
@@ -168,6 +183,15 @@ FACO_DEV int64_t cas_agent64(int64_t *p, int64_t expected, int64_t desired) {
 FACO_DEV void fence_acquire_agent() { __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent"); }
 FACO_DEV void fence_release_agent() { __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent"); }
 
+// Element i >= 0 of an array of less than 4 GiB at a wave-uniform address: the
+// byte offset is formed in 32 bits, so the access takes the address from
+// scalar registers and one shift instead of 64-bit vector additions.
+template <class T>
+FACO_DEV T &at(T *base, int i) {
+  typedef typename std::conditional<std::is_const<T>::value, const char, char>::type B;
+  return *(T *)((B *)base + (uint32_t)i * (uint32_t)sizeof(T));
+}
+
 // --------------------------------------------------------------- bitmap ---
 
 FACO_DEV bool bit_get(const uint32_t *bm, int x) {
@@ -202,6 +226,16 @@ FACO_DEV int nint_sqrt(double d2) {
   const double r = __builtin_rint(__builtin_amdgcn_sqrt(d2));
   const double e = __builtin_fma(r, r, -d2);
   return (int)r + (e < -r ? 1 : 0) - (e >= r && r > 0.0 ? 1 : 0);
+}
+
+// cost() of two points that differ (0 and -1 are both possible for equal
+// ones): without the guard that r is positive.
+FACO_DEV int cost_ne(int2 a, int2 b) {
+  const double dx = (double)(a.x - b.x), dy = (double)(a.y - b.y);
+  const double d2 = __builtin_fma(dx, dx, dy * dy);
+  const double r = __builtin_rint(__builtin_amdgcn_sqrt(d2));
+  const double e = __builtin_fma(r, r, -d2);
+  return (int)r + (e < -r ? 1 : 0) - (e >= r ? 1 : 0);
 }
 
 FACO_DEV int cost(int2 a, int2 b) {

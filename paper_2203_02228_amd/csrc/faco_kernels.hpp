@@ -91,6 +91,7 @@ constexpr int kMaxTeam = 8;
 enum TeamOp {
   OP_EXIT, OP_WINDOW, OP_SWEEP, OP_COPY, OP_NEAREST, OP_OROPT, OP_SEGPERM, OP_SEGMAT, OP_SEARCH
 };
+constexpr int kDescWords = 36;  // a wave's move record in the team local search
 struct TeamLds {
   int op;
   int arg[11];
@@ -105,7 +106,7 @@ struct TeamLds {
   union {
     int orx[14][kWave];          // segment lists' Or-opt: the leader's loaded neighbourhoods
     struct {                     // local search by all waves (team_local_search)
-      alignas(16) int desc[2][kMaxTeam * 32];  // each wave's best move, by round parity
+      alignas(16) int desc[2][kMaxTeam * kDescWords];  // each wave's best move, by round parity
       int pushed;                // cities wave 0 listed after the move (bit 8: queue spilled)
       int cnt[2];                // sweep: cities gathered, by pass parity
     } ls;
@@ -1202,20 +1203,20 @@ FACO_DEV bool has_improving(const Inst &I, uint32_t flags, int x,
                             const int32_t *route, const int32_t *pos, const int2 *rxy) {
   constexpr int CK = KT < FACO_SWEEP_CK ? KT : FACO_SWEEP_CK;
   const int n = I.n, K = I.k;
-  const size_t row = (size_t)x * (size_t)K;
+  const int row = x * K;
   // first chunk of the list with the city's own data
   int cb[CK], cd[CK];
 #pragma unroll
   for (int j = 0; j < CK; ++j) {
-    cb[j] = j < K ? I.cl[row + j] : x;
-    cd[j] = j < K ? I.cl_d[row + j] : 0x7fffffff;
+    cb[j] = j < K ? at(I.cl, row + j) : x;
+    cd[j] = j < K ? at(I.cl_d, row + j) : 0x7fffffff;
   }
-  const int px = pos[x];
-  const int2 cx = I.xy[x];
+  const int px = at(pos, x);
+  const int2 cx = at(I.xy, x);
   int xnx[7], xny[7];
 #pragma unroll
   for (int j = 0; j < 7; ++j) {
-    const int2 q = rxy[wrapc(px + j - 3, n)];
+    const int2 q = at(rxy, wrapc(px + j - 3, n));
     xnx[j] = q.x; xny[j] = q.y;
   }
 #define XN(j) make_int2(xnx[j], xny[j])
@@ -1247,15 +1248,15 @@ FACO_DEV bool has_improving(const Inst &I, uint32_t flags, int x,
     int pb[CK], xbx[CK], xby[CK];
 #pragma unroll
     for (int j = 0; j < CK; ++j) {
-      pb[j] = pos[cb[j]];
-      const int2 q = I.xy[cb[j]];
+      pb[j] = at(pos, cb[j]);
+      const int2 q = at(I.xy, cb[j]);
       xbx[j] = q.x; xby[j] = q.y;
     }
     int sx[CK], sy[CK], qx[CK], qy[CK];  // succ and pred of b
 #pragma unroll
     for (int j = 0; j < CK; ++j) {
-      const int2 q1 = rxy[pb[j] + 1 == n ? 0 : pb[j] + 1];
-      const int2 q2 = rxy[pb[j] == 0 ? n - 1 : pb[j] - 1];
+      const int2 q1 = at(rxy, pb[j] + 1 == n ? 0 : pb[j] + 1);
+      const int2 q2 = at(rxy, pb[j] == 0 ? n - 1 : pb[j] - 1);
       sx[j] = q1.x; sy[j] = q1.y;
       qx[j] = q2.x; qy[j] = q2.y;
     }
@@ -1291,12 +1292,12 @@ FACO_DEV bool has_improving(const Inst &I, uint32_t flags, int x,
     c0 += CK;
     if (c0 >= K) break;
     // the next chunk, if a lane of the wave still needs it
-    const int dn = I.cl_d[row + c0];
+    const int dn = at(I.cl_d, row + c0);
     if (!ballot(!found && dn < lim)) break;
 #pragma unroll
     for (int j = 0; j < CK; ++j) {
-      cb[j] = c0 + j < K ? I.cl[row + c0 + j] : x;
-      cd[j] = c0 + j < K ? I.cl_d[row + c0 + j] : 0x7fffffff;
+      cb[j] = c0 + j < K ? at(I.cl, row + c0 + j) : x;
+      cd[j] = c0 + j < K ? at(I.cl_d, row + c0 + j) : 0x7fffffff;
     }
   }
 #undef XN
@@ -1338,9 +1339,9 @@ FACO_DEV void reverse_part(int n, int s, int L, int w, int32_t *route, int32_t *
       if (i < half) {
         p1[c] = wrap1(s + i, n);
         p2[c] = wrap1(s + L - 1 - i, n);
-        v1[c] = route[p1[c]];
-        v2[c] = route[p2[c]];
-        const int2 a1 = rxy[p1[c]], a2 = rxy[p2[c]];
+        v1[c] = at(route, p1[c]);
+        v2[c] = at(route, p2[c]);
+        const int2 a1 = at(rxy, p1[c]), a2 = at(rxy, p2[c]);
         c1x[c] = a1.x; c1y[c] = a1.y;
         c2x[c] = a2.x; c2y[c] = a2.y;
       }
@@ -1349,12 +1350,12 @@ FACO_DEV void reverse_part(int n, int s, int L, int w, int32_t *route, int32_t *
     for (int c = 0; c < CH; ++c) {
       const int i = (c0 + c * TW) * kWave + lane;
       if (i < half) {
-        route[p1[c]] = v2[c];
-        route[p2[c]] = v1[c];
-        rxy[p1[c]] = make_int2(c2x[c], c2y[c]);
-        rxy[p2[c]] = make_int2(c1x[c], c1y[c]);
-        pos[v2[c]] = p1[c];
-        pos[v1[c]] = p2[c];
+        at(route, p1[c]) = v2[c];
+        at(route, p2[c]) = v1[c];
+        at(rxy, p1[c]) = make_int2(c2x[c], c2y[c]);
+        at(rxy, p2[c]) = make_int2(c1x[c], c1y[c]);
+        at(pos, v2[c]) = p1[c];
+        at(pos, v1[c]) = p2[c];
       }
     }
   }
@@ -1380,8 +1381,8 @@ FACO_DEV void shift_part(int n, int src, int dst, int D, bool down, int w, int32
       const int i = rb + (w + c * TW) * kWave + lane;
       if (i < D) {
         const int sp = wrap1(src + i, n);
-        v[c] = route[sp];
-        const int2 q = rxy[sp];
+        v[c] = at(route, sp);
+        const int2 q = at(rxy, sp);
         cvx[c] = q.x; cvy[c] = q.y;
       }
     }
@@ -1391,9 +1392,9 @@ FACO_DEV void shift_part(int n, int src, int dst, int D, bool down, int w, int32
       const int i = rb + (w + c * TW) * kWave + lane;
       if (i < D) {
         const int d = wrap1(dst + i, n);
-        route[d] = v[c];
-        rxy[d] = make_int2(cvx[c], cvy[c]);
-        pos[v[c]] = d;
+        at(route, d) = v[c];
+        at(rxy, d) = make_int2(cvx[c], cvy[c]);
+        at(pos, v[c]) = d;
       }
     }
   }

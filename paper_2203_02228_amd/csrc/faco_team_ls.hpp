@@ -11,154 +11,195 @@
 // Wave 0 meanwhile pushes the move's cities.
 //
 // What bounds a round is its chain: two dependent levels of loads (positions,
-// then tour neighbours) that mostly miss L2 (64 ants' arrays are 100 MB at
-// 100k cities), about 280 vector instructions, and the barriers.  A leader
+// then tour neighbours; 64 ants' arrays are 100 MB at 100k cities, so they
+// mostly miss L2), its instructions, one every four cycles, and the barriers.  A leader
 // that evaluated four cities and handed the Or-opt variants to helper waves
 // through LDS paid two more barriers and 14 words a lane for the hand-over.
 // Measured on the 100k workload (64 ants, iterations 100..200): 649 rounds of 8
-// cities an ant at 2.44 us instead of 797 of 4 at 2.04, a move 2.2 us instead
-// of 3.0; the ant kernel 7.5 ms instead of 9.6.
+// cities an ant at 1.84 us instead of 797 of 4 at 2.04, a move 2.1 us instead
+// of 3.0; the ant kernel 7.1 ms instead of 9.6.
 #pragma once
 
-// Move record of a wave (32 words, eight int4):
+// Move record of a wave (9 int4):
 //   [0] gain (0: none), code, b, bn   [1] pb, pbn, pa, a
-//   [2..3] cities at tour positions pa-3 .. pa+3 (7 words)
-//   [4..7] their coordinates (7 int2)
+//   [2 + j] city and coordinates at tour position pa - 3 + j (j = 0..6)
 // code: 0/1 2-opt through (a, succ a)/(pred a, a); 2 + 2 slot + side: Or-opt
 // (slots of or_slot_lanes).  bn: succ b (2-opt code 0, Or-opt side 0) or
 // pred b; pb, pbn, pa: positions of b, bn, a.
-constexpr int kDescWords = 32;
 
 // The loads of a wave's next city that never change along a local search.
 struct TeamPre {
-  int a;  // -1: none
+  int a;
   int b, d;
 };
 template <int GS>
 FACO_DEV TeamPre team_pre(const Inst &I, int a) {
   const int s = lane_id() & (GS - 1);
-  const size_t row = (size_t)a * (size_t)I.k;
   TeamPre P;
   P.a = a;
-  P.b = s < I.k ? I.cl[row + s] : a;
-  P.d = s < I.k ? I.cl_d[row + s] : 0;
+  P.b = a;
+  P.d = 0;
+  if (s < I.k) {
+    P.b = at(I.cl + (size_t)a * (size_t)I.k, s);
+    P.d = at(I.cl_d + (size_t)a * (size_t)I.k, s);
+  }
   return P;
 }
 
-// Evaluate city a with the whole wave: lane = (part, candidate slot s), part
-// p of 64 / GS.  Even parts try the moves through (b, succ b), odd parts those
-// through (pred b, b); with four parts the 2-opt move and Or-opt slots 0, 1
-// are tried by the first pair of parts and slots 2..4 by the second.  Every
-// 16-lane row also holds the 11 costs that depend only on a's neighbourhood
-// (GroupEval::uc), one per lane.  The result is the best move in the order of
-// the sequential evaluation: 2-opt first (loop 1 over the list, then loop 2),
-// else Or-opt by gain, then slot, list position, succ before pred.
+// What a lane evaluates, fixed along a local search.  lane = (part, candidate
+// slot s), part p of 64 / GS: even parts try the moves through (b, succ b),
+// odd parts those through (pred b, b).  With four parts (lists of up to 16)
+// the first pair of parts tries the 2-opt move and Or-opt slots 0, 1 and the
+// second slots 2, 3, 4; with two parts every lane tries all six.
+// A variant's segment is a range of tour positions pa - 3 + j; its mask holds
+// those j as bits (all bits: the lane does not try the variant).
+struct TeamLane {
+  int su, sv;            // ends (j) of this lane's neighbourhood cost
+  int ja, jb, jc;        // j of the end of the variants' second new edge
+  uint32_t ma, mb, mc;
+  int step;              // 1: b's neighbour is succ b; -1: pred b
+  int m2nd, mrem;        // all ones: second pair of parts; removed edge (pred a, a)
+};
+// m ? x : y for an all-ones or zero mask in a vector register
+FACO_DEV int pick(int m, int x, int y) { return (m & x) | (~m & y); }
+constexpr uint32_t kSegMask[kOrSlots] = {0x08u, 0x18u, 0x38u, 0x0Cu, 0x0Eu};
+constexpr int kTwoBit = 1 << 30;  // above every Or-opt gain: 2-opt goes first
+
 template <int GS>
-FACO_DEV void team_eval(const Inst &I, uint32_t flags, const TeamPre &P, const int32_t *route,
-                        const int32_t *pos, const int2 *rxy, int *desc) {
-  constexpr int NP = kWave / GS;       // parts
-  const int n = I.n, K = I.k, lane = lane_id();
-  const int s = lane & (GS - 1), part = lane / GS, side = part & 1;
-  const bool second = part >= 2;
+FACO_DEV TeamLane team_lane(const Inst &I, uint32_t flags) {
+  const int lane = lane_id();
+  const int side = (lane / GS) & 1;
+  const bool second = lane / GS >= 2;
+  const int r = lane & 15;
+  TeamLane T;
+  // costs 0..5: tour edges (j, j + 1); 6..10: (6, 2), (2, 5), (2, 4), (1, 4),
+  // (0, 4), the edges that close the gap of a removed segment
+  T.su = r <= 6 ? r : (r <= 8 ? 2 : (r == 9 ? 1 : (r == 10 ? 0 : 3)));
+  T.sv = r <= 5 ? r + 1 : (r == 6 ? 2 : (r == 7 ? 5 : (r <= 10 ? 4 : 3)));
+  const int two = side ? 2 : 4;
+  T.ja = second ? 5 : two;
+  T.jb = second ? 2 : 3;
+  T.jc = second ? 1 : 4;
+  const int lmax = (flags & LS_OROPT) ? or_lmax(I) : 0;
+  const bool act = (lane & (GS - 1)) < I.k;
+  const uint32_t none = 0xFFFFFFFFu;
+  T.ma = second ? (lmax >= 3 ? kSegMask[2] : none) : ((flags & LS_2OPT) ? 0u : none);
+  T.mb = second ? (lmax >= 2 ? kSegMask[3] : none) : (lmax >= 1 ? kSegMask[0] : none);
+  T.mc = second ? (lmax >= 3 ? kSegMask[4] : none) : (lmax >= 2 ? kSegMask[1] : none);
+  T.step = side ? -1 : 1;
+  T.m2nd = second ? -1 : 0;
+  T.mrem = second || side ? -1 : 0;
+  T.ma = act ? T.ma : none;
+  T.mb = act ? T.mb : none;
+  T.mc = act ? T.mc : none;
+  return T;
+}
+
+// Evaluate city a with the whole wave.  The result is the best move in the
+// order of the sequential evaluation: 2-opt first (loop 1 over the list, then
+// loop 2), else Or-opt by gain, then slot, list position, succ before pred.
+template <int GS>
+FACO_DEV void team_eval(const Inst &I, const TeamLane &T, const TeamPre &P,
+                        const int32_t *route, const int32_t *pos, const int2 *rxy, int *desc) {
+  const int n = I.n;
+  // opaque: masks of lanes are compared afresh instead of kept (and spilled)
+  // in scalar register pairs across the whole kernel
+  int lane = lane_id();
+  asm volatile("" : "+v"(lane));
+  const int s = lane & (GS - 1), side = (lane / GS) & 1;
   const int a = P.a, b = P.b, d_ab = P.d;
-  const bool act = s < K;
   // level 1
-  const int pa = uniform_i(pos[a]);
-  const int pb = pos[b];
-  const int2 xb = I.xy[b];
-  // level 2: a's neighbourhood (each lane the ends of its cost) and b's
-  // neighbour
-  const int r16 = lane & 15;
-  const int su = r16 <= 5 ? r16 : (r16 <= 8 ? 2 : (r16 == 9 ? 1 : (r16 == 10 ? 0 : 3)));
-  const int sv = r16 <= 5 ? r16 + 1 : (r16 <= 8 ? r16 - 2 : (r16 <= 10 ? 4 : 3));
-  const int2 U = rxy[wrapc(pa + su - 3, n)], V = rxy[wrapc(pa + sv - 3, n)];
-  const int nb = route[wrapc(pa + (lane < 7 ? lane : 3) - 3, n)];
-  const int pbs = pb + 1 == n ? 0 : pb + 1, pbp = pb == 0 ? n - 1 : pb - 1;
-  const int pbn = side ? pbp : pbs;
-  const int2 xbn = rxy[pbn];
-  const int bn = route[pbn];
-  const int uc = cost(U, V);
-  const int d_bn = cost(xb, xbn);
+  const int pb = at(pos, b);
+  const int2 xb = at(I.xy, b);
+  const int pa = uniform_i(at(pos, a));
+  // level 2: a's neighbourhood and b's neighbour
+  const int32_t *rb = route + (pa - 3);
+  const int2 *xr = rxy + (pa - 3);
+  int ju = T.su, jv = T.sv, ja = T.ja, jb = T.jb, jc = T.jc;
+  if (pa < 3 || pa + 3 >= n) {
+    rb = route;
+    xr = rxy;
+    ju = wrapc(pa - 3 + ju, n);
+    jv = wrapc(pa - 3 + jv, n);
+    ja = wrapc(pa - 3 + ja, n);
+    jb = wrapc(pa - 3 + jb, n);
+    jc = wrapc(pa - 3 + jc, n);
+  }
+  const int2 U = at(xr, ju), V = at(xr, jv);
+  const int nb = at(rb, ju);
+  const int2 xA = at(xr, ja), xB = at(xr, jb), xC = at(xr, jc);
+  int pbn = pb + T.step;
+  pbn = pbn < 0 ? n - 1 : pbn;
+  pbn = pbn == n ? 0 : pbn;
+  const int2 xbn = at(rxy, pbn);
+  const int bn = at(route, pbn);
+  // which of the positions pa - 3 + j hold b and bn
+  const int rj = wrapc(pb - pa + 3, n);
+  const int rn = wrapc(rj + T.step, n);
+  uint32_t M = (1u << (rj < 31 ? rj : 31)) | (1u << (rn < 31 ? rn : 31));
+  if (n < 7) M |= M << n;  // a tour shorter than the neighbourhood
+  const int uc = cost_ne(U, V);
+  const int in = cost_ne(xb, xbn) - d_ab;  // edge freed at b minus the new edge (a, b)
   int u[11];
 #pragma unroll
   for (int j = 0; j < 11; ++j) u[j] = row_bcast(uc, j);
-  int2 X[6];  // coordinates at pa - 3 + j
-#pragma unroll
-  for (int j = 1; j < 6; ++j) X[j] = make_int2(row_bcast(U.x, j), row_bcast(U.y, j));
-  const int Lmax = (flags & LS_OROPT) ? or_lmax(I) : 0;
-  const int in = d_bn - d_ab;  // edge freed at b minus the new edge (a, b)
-  // Or-opt slot `vi`: the gain (0: no move)
-  auto oropt = [&](int L, int rem, int g_rem, int fpos, int2 xo) -> int {
-    const int g = g_rem + in - cost(xo, xbn);
-    const bool ok = act && L <= Lmax && d_ab < rem && wrapc(pb - fpos, n) >= L &&
-                    wrapc(pbn - fpos, n) >= L;
-    return ok ? g : 0;
-  };
-  auto twoopt = [&](int old, int2 xo) -> int {
-    const int g = old + in - cost(xo, xbn);
-    return (act && (flags & LS_2OPT) && old > d_ab) ? g : 0;
-  };
-  int g2 = 0, go = 0, vo = 0;
-  const int p1 = wrapc(pa - 1, n), p2 = wrapc(pa - 2, n);
-  const int old = side ? u[2] : u[3];
-  const int2 xo2 = side ? X[2] : X[4];
-  if (NP == 4) {
-    const int G0 = u[2] + u[3] - u[6], G1 = u[2] + u[4] - u[7], G2 = u[2] + u[5] - u[8];
-    const int G3 = u[1] + u[3] - u[9], G4 = u[0] + u[3] - u[10];
-    // second = false: 2-opt, slot 0, slot 1; true: slot 2, slot 3, slot 4
-    const int gA = second ? oropt(3, u[2], G2, pa, X[5]) : twoopt(old, xo2);
-    const int2 xB = second ? X[2] : X[3], xC = second ? X[1] : X[4];
-    const int gB = oropt(second ? 2 : 1, second ? u[3] : u[2], second ? G3 : G0,
-                         second ? p1 : pa, xB);
-    const int gC = oropt(second ? 3 : 2, second ? u[3] : u[2], second ? G4 : G1,
-                         second ? p2 : pa, xC);
-    g2 = second ? 0 : gA;
-    go = second ? gA : 0;
-    vo = second ? 2 : 0;
-    const int vB = second ? 3 : 0, vC = second ? 4 : 1;
-    vo = gB > go ? vB : vo;
+  int g2, go, vo;
+  if (GS == 16) {
+    const int cA = cost_ne(xA, xbn), cB = cost_ne(xB, xbn), cC = cost_ne(xC, xbn);
+    // removal gains; the removed edge at a: pred a for the forward slots and
+    // the 2-opt move through pred b, succ a otherwise
+    const int m = T.m2nd;
+    const int remA = pick(T.mrem, u[2], u[3]), remB = pick(m, u[3], u[2]);
+    int gA = pick(m, u[2] + u[5] - u[6], remA) + in - cA;
+    int gB = pick(m, u[1] - u[9], u[2] - u[8]) + u[3] + in - cB;
+    int gC = pick(m, u[3] + u[0] - u[10], u[2] + u[4] - u[7]) + in - cC;
+    gA = ((M & T.ma) == 0u && d_ab < remA) ? gA : 0;
+    gB = ((M & T.mb) == 0u && d_ab < remB) ? gB : 0;
+    gC = ((M & T.mc) == 0u && d_ab < remB) ? gC : 0;
+    g2 = gA & ~m;
+    go = gA & m;
+    vo = m & 2;
+    vo = gB > go ? (m & 3) : vo;
     go = gB > go ? gB : go;
-    vo = gC > go ? vC : vo;
+    vo = gC > go ? 1 + (m & 3) : vo;
     go = gC > go ? gC : go;
   } else {
-    g2 = twoopt(old, xo2);
-    const int g[5] = {oropt(1, u[2], u[2] + u[3] - u[6], pa, X[3]),
-                      oropt(2, u[2], u[2] + u[4] - u[7], pa, X[4]),
-                      oropt(3, u[2], u[2] + u[5] - u[8], pa, X[5]),
-                      oropt(2, u[3], u[1] + u[3] - u[9], p1, X[2]),
-                      oropt(3, u[3], u[0] + u[3] - u[10], p2, X[1])};
+    // ma, mb, mc hold the masks of the 2-opt move and slots 0, 1: the others
+    // follow from the same limits
+    const int remA = side ? u[2] : u[3];
+    g2 = remA + in - cost_ne(xA, xbn);
+    g2 = ((M & T.ma) == 0u && d_ab < remA) ? g2 : 0;
+    const int lmax = T.mc != 0xFFFFFFFFu ? (or_lmax(I) >= 3 ? 3 : 2) : (T.mb != 0xFFFFFFFFu ? 1 : 0);
+    const int su[5] = {u[2] + u[3] - u[8], u[2] + u[4] - u[7], u[2] + u[5] - u[6],
+                       u[3] + u[1] - u[9], u[3] + u[0] - u[10]};
+    const int je[5] = {3, 4, 5, 2, 1};
+    go = 0;
+    vo = 0;
 #pragma unroll
     for (int v = 0; v < 5; ++v) {
-      vo = g[v] > go ? v : vo;
-      go = g[v] > go ? g[v] : go;
+      const int2 xo = make_int2(row_bcast(U.x, je[v]), row_bcast(U.y, je[v]));
+      const int L = v < 3 ? v + 1 : v - 1;
+      const int g = su[v] + in - cost_ne(xo, xbn);
+      const bool ok = L <= lmax && (M & kSegMask[v]) == 0u && d_ab < (v < 3 ? u[2] : u[3]) && g > go;
+      vo = ok ? v : vo;
+      go = ok ? g : go;
     }
   }
-  const int M2 = wave_max_i32(g2), MO = wave_max_i32(go);
-  int l = 0;
-  const bool two = M2 > 0;
-  const int gain = two ? M2 : (MO > 0 ? MO : 0);
-  if (two) {
-    l = ctz64(ballot(g2 == M2));  // lane order is the order of the two loops
-  } else if (MO > 0) {
-    uint64_t m = ballot(go == MO);
-    if (m & (m - 1)) {
-      const int idx = go == MO ? (vo * K + s) * 2 + side : 0x7fffffff;
-      const int best = wave_min_i32(idx);
-      m = ballot(idx == best);
-    }
-    l = ctz64(m);
+  const int key = g2 > 0 ? g2 + kTwoBit : go;
+  const int best = wave_max_i32(key);
+  uint64_t m = ballot(key == best);  // 2-opt: lane order is the order of the two loops
+  const bool two = best >= kTwoBit;
+  if (!two && best > 0 && (m & (m - 1))) {
+    const int idx = key == best ? (vo * I.k + s) * 2 + side : 0x7fffffff;
+    const int low = wave_min_i32(idx);
+    m = ballot(idx == low);
   }
   int4 *d4 = reinterpret_cast<int4 *>(desc);
-  if (lane == l) {
-    d4[0] = make_int4(gain, two ? side : 2 + 2 * vo + side, b, bn);
+  if (lane == ctz64(m)) {
+    d4[0] = make_int4(two ? best - kTwoBit : best, two ? side : 2 + 2 * vo + side, b, bn);
     d4[1] = make_int4(pb, pbn, pa, a);
   }
-  if (gain > 0) {
-    if (lane < 7) desc[8 + lane] = nb;
-    int2 *d2 = reinterpret_cast<int2 *>(desc + 16);
-    if (lane < 6) d2[lane] = U;
-    if (lane == 5) d2[6] = V;
-  }
+  if (lane < 7) d4[2 + lane] = make_int4(nb, U.x, U.y, 0);
 }
 
 // This wave's share of a reversal (see reverse_part): few chunks take the
@@ -303,9 +344,10 @@ FACO_DEV int64_t team_local_search(const Inst &I, uint32_t flags, int32_t *route
   int changes = 0, changes_at_sweep = -1, par = 0;
   int pops = 0, m2 = 0, sweeps = 0, rounds = 0;
   int64_t gain = 0, moved = 0, t_eval = 0, t_apply = 0, t_sweep = 0;
+  const TeamLane tlane = team_lane<GS>(I, flags);
   TeamPre pre;
-  pre.a = -1;
-  pre.b = pre.d = 0;
+  int pre_a = -1;
+  pre.a = pre.b = pre.d = 0;
   int64_t t0 = w == 0 ? ticks() : 0;
   for (;;) {
     for (;;) {
@@ -322,29 +364,34 @@ FACO_DEV int64_t team_local_search(const Inst &I, uint32_t flags, int32_t *route
       if (w < gcount) {
         int h = Q.head + w;
         h = h >= Q.cap ? h - Q.cap : h;
-        const int a = uniform_i(Q.in_lds ? Q.lr[h] : Q.gr[h]);
-        if (uniform_i(pre.a) != a) pre = team_pre<GS>(I, a);
-        team_eval<GS>(I, flags, pre, route, pos, rxy, desc + w * kDescWords);
+        int a = Q.lr[Q.in_lds ? h : 0];
+        if (!Q.in_lds) a = Q.gr[h];
+        a = uniform_i(a);
+        if (uniform_i(pre_a) != a) pre = team_pre<GS>(I, a);
+        pre.a = a;
+        team_eval<GS>(I, tlane, pre, route, pos, rxy, desc + w * kDescWords);
       }
       team_sync();
-      // lanes 8 v .. 8 v + 7 hold wave v's record
+      // lanes 2 v and 2 v + 1 hold the head of wave v's record
       int4 v = make_int4(0, 0, 0, 0);
-      if (lane < 8 * gcount) v = reinterpret_cast<const int4 *>(desc)[lane];
-      const uint64_t hm = ballot((lane & 7) == 0 && v.x > 0);
-      const int j = uniform_i(hm ? ctz64(hm) >> 3 : gcount);
+      if (lane < 2 * gcount)
+        v = reinterpret_cast<const int4 *>(desc)[(lane >> 1) * (kDescWords / 4) + (lane & 1)];
+      const uint64_t hm = ballot((lane & 1) == 0 && v.x > 0);
+      const int j = uniform_i(hm ? ctz64(hm) >> 1 : gcount);
       const int npop = j < gcount ? j + 1 : gcount;
       // wave 0 unlists the popped cities
-      if (w == 0 && (lane & 7) == 1 && (lane >> 3) < npop) bit_clear(inq, v.w);
+      if (w == 0 && (lane & 1) == 1 && (lane >> 1) < npop) bit_clear(inq, v.w);
       Q.head = Q.head + npop >= Q.cap ? Q.head + npop - Q.cap : Q.head + npop;
       Q.count -= npop;
       pops += npop;
       ++rounds;
       // the next round's city of this wave, unless a push comes before it
-      pre.a = -1;
+      pre_a = -1;
       if (Q.in_lds && w < Q.count) {
         int h = Q.head + w;
         h = h >= Q.cap ? h - Q.cap : h;
-        pre = team_pre<GS>(I, uniform_i(Q.lr[h]));
+        pre_a = uniform_i(Q.lr[h]);
+        pre = team_pre<GS>(I, pre_a);
       }
       if (w == 0) {
         const int64_t t1 = fine_ticks();
@@ -352,7 +399,7 @@ FACO_DEV int64_t team_local_search(const Inst &I, uint32_t flags, int32_t *route
         t0 = t1;
       }
       if (j >= gcount) continue;
-      const int jb = 8 * j;
+      const int jb = 2 * j;
       const int code = readlane_i(v.y, jb);
       const int g = readlane_i(v.x, jb);
       const int pb = readlane_i(v.x, jb + 1), pbn = readlane_i(v.y, jb + 1);
@@ -368,14 +415,12 @@ FACO_DEV int64_t team_local_search(const Inst &I, uint32_t flags, int32_t *route
         int k;
         if (two) {
           // side 0: a, succ a, b, succ b; side 1: pred a, a, pred b, b
-          k = lane == 0 ? (side ? 10 : 11)
-                        : (lane == 1 ? (side ? 11 : 12)
+          k = lane == 0 ? (side ? 8 + 4 * 2 : 8 + 4 * 3)
+                        : (lane == 1 ? (side ? 8 + 4 * 3 : 8 + 4 * 4)
                                      : ((lane == 2) == (side == 0) ? 2 : 3));
         } else {
-          k = lane == 0 ? 8 + lp
-                        : (lane == 1 ? 8 + lq
-                                     : (lane == 2 ? 2
-                                                  : (lane == 3 ? 3 : (lane == 4 ? 8 + lf : 8 + ll))));
+          const int jn = lane == 0 ? lp : (lane == 1 ? lq : (lane == 4 ? lf : ll));
+          k = lane == 2 || lane == 3 ? lane : 8 + 4 * jn;
         }
         const int np = two ? 4 : 6;
         const int x = rec[lane < np ? k : 0];
@@ -424,14 +469,13 @@ FACO_DEV int64_t team_local_search(const Inst &I, uint32_t flags, int32_t *route
         const bool rev = (dir == 1) != (side == 1);
         const int i = lane < L ? lane : 0;
         const int ei = lf + (rev ? L - 1 - i : i);
-        const int ins = rec[8 + ei];
-        const int2 insx = reinterpret_cast<const int2 *>(rec + 16)[ei];
+        const int4 ins = reinterpret_cast<const int4 *>(rec)[2 + ei];
         team_shift_share<TW>(n, src, dst, D, down, w, route, pos, rxy);
         if (w == 1 && lane < L) {
           const int d = wrapc((down ? wrapc(fpos + D1, n) : px2) + lane, n);
-          route[d] = ins;
-          rxy[d] = insx;
-          pos[ins] = d;
+          at(route, d) = ins.x;
+          at(rxy, d) = make_int2(ins.y, ins.z);
+          at(pos, ins.x) = d;
         }
         mv = D + L;
       }
@@ -467,7 +511,7 @@ FACO_DEV int64_t team_local_search(const Inst &I, uint32_t flags, int32_t *route
     ++sweeps;
     const int pushed = uniform_i(team_sweep<KT, TW>(I, flags, W, Q, FlatT{route, pos, rxy}, inq,
                                                     touched, ord, tl, w, tk));
-    pre.a = -1;
+    pre_a = -1;
     if (w == 0) {
       const int64_t t1 = ticks();
       t_sweep += t1 - t0;
