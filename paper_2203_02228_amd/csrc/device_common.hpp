@@ -137,6 +137,7 @@ FACO_DEV uint64_t uniform_u64(uint64_t v) {
   const uint32_t hi = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(v >> 32));
   return ((uint64_t)hi << 32) | lo;
 }
+FACO_DEV int64_t uniform_i64(int64_t v) { return (int64_t)uniform_u64((uint64_t)v); }
 
 // Workgroup barrier; global and LDS writes before it are visible to every
 // wave of the workgroup after it.

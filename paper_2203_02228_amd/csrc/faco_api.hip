@@ -338,10 +338,10 @@ extern "C" uint64_t faco_footprint_bytes(int32_t n, const faco_params *p) {
   const uint64_t N = (uint64_t)n, A = (uint64_t)p->n_ants;
   uint64_t b = 0;
   b += align_up(8 * N);                    // xy
-  b += align_up(16 * ((N + 31) / 32));     // bounding boxes of 32-label words
+  b += 2 * align_up(16 * ((N + 31) / 32));  // bounding boxes of 32 labels, of 32 source positions
   const uint64_t NB = (N + 63) / 64 * 64;   // source-ordered tables: whole 64-position blocks
   b += 4 * align_up(4 * N * (uint64_t)k);   // cl, cost, eta, tau
-  b += 4 * align_up(4 * NB * (uint64_t)k);  // source-ordered city, weight, position, cost
+  b += 2 * align_up(4 * NB * (((uint64_t)k + 3) & ~(uint64_t)3));  // source-ordered weight, position
   b += align_up(4 * N * (uint64_t)bl + 4); // backup lists
   b += 4 * align_up(4 * N) + 2 * align_up(8 * N); // source route/pos/edge costs/coordinates, adjacency, global best
   b += 2 * align_up(4 * N);                   // label maps
@@ -370,7 +370,7 @@ static int enqueue_iteration(faco_instance *h) {
   const Inst &I = h->dv;
   const int n = h->n;
   const unsigned nb_src = (unsigned)((n + 255) / 256);
-  const size_t slots = (size_t)n * (size_t)h->k;
+  const size_t slots = (size_t)n * (size_t)I.ks;
   const unsigned nb_tau = (unsigned)((slots + 255) / 256);
   TimedLaunch tl;
   if (h->timing) begin_timed(h, 0, tl);
@@ -470,11 +470,13 @@ extern "C" int faco_build_instance(const int32_t *xy, int32_t n, const faco_para
     return set_err(nullptr, FACO_EDEVICE, "hipGetDevice failed");
   }
   const size_t N = (size_t)n, A = (size_t)p->n_ants, K = (size_t)h->k, BL = (size_t)h->bl;
+  const size_t KS = (K + 3) & ~(size_t)3;
   const size_t NB = (N + 63) / 64 * 64;
 
   Inst &I = h->dv;
   I.n = n;
   I.k = h->k;
+  I.ks = (h->k + 3) & ~3;
   I.bl = h->bl;
   I.A = p->n_ants;
   I.m = p->min_new_edges;
@@ -509,16 +511,15 @@ extern "C" int faco_build_instance(const int32_t *xy, int32_t n, const faco_para
   ALLOC(eta, float, N * K);
   ALLOC(cl_d, int32_t, N * K);
   ALLOC(tau, float, N * K);
-  ALLOC(scl, int32_t, NB * K);
-  ALLOC(sw, float, NB * K);
-  ALLOC(ssp, int32_t, NB * K);
-  ALLOC(sd, int32_t, NB * K);
+  ALLOC(sw, float, NB * KS);
+  ALLOC(ssp, int32_t, NB * KS);
   ALLOC(src_route, int32_t, N);
   ALLOC(src_pos, int32_t, N);
   ALLOC(gb_route, int32_t, N);
   ALLOC(src_adj, int2, N);
   ALLOC(src_d, int32_t, N);
   ALLOC(src_xy, int2, N);
+  ALLOC(sbox, int4, (N + 31) / 32);
   ALLOC(routes, int32_t, N * A);
   ALLOC(pos, int32_t, N * A);
   ALLOC(ring, int32_t, N * A);
@@ -642,7 +643,7 @@ extern "C" int faco_build_instance(const int32_t *xy, int32_t n, const faco_para
   hipLaunchKernelGGL(faco::init_state_kernel, dim3(1), dim3(1), 0, h->stream, I);
   hipLaunchKernelGGL(faco::source_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0,
                      h->stream, I, 1);
-  const size_t slots = N * K;
+  const size_t slots = N * KS;
   hipLaunchKernelGGL(faco::pheromone_kernel, dim3((unsigned)((slots + 255) / 256)), dim3(256),
                      0, h->stream, I, 1);
   BTRY(hipGetLastError());
@@ -1030,7 +1031,7 @@ static void batch_shape(faco_instance *const *hs, int32_t count, Inst *insts, in
     }
     const size_t words = 3 * (size_t)((h->n + 31) / 32) + (size_t)insts[i].lcap;
     B.lds_words = words > B.lds_words ? words : B.lds_words;
-    const size_t slots = (size_t)h->n * (size_t)h->k;
+    const size_t slots = (size_t)h->n * (size_t)h->dv.ks;
     B.max_slots = slots > B.max_slots ? slots : B.max_slots;
     if (amap)
       for (int a = 0; a < h->p.n_ants; ++a) amap[w++] = make_int2(i, a);

@@ -14,7 +14,7 @@ __global__ void __launch_bounds__(256) source_kernel(Inst I, int init) {
 }
 
 __global__ void __launch_bounds__(256) pheromone_kernel(Inst I, int init) {
-  run_pheromone(I, (size_t)blockIdx.x * blockDim.x + threadIdx.x, init);
+  run_pheromone(I, blockIdx.x * blockDim.x + threadIdx.x, init);
 }
 
 // Limits of the initial solution; state before the first iteration.
@@ -123,7 +123,7 @@ __global__ void __launch_bounds__(256) source_batch_kernel(const Inst *insts) {
 }
 
 __global__ void __launch_bounds__(256) pheromone_batch_kernel(const Inst *insts) {
-  run_pheromone(insts[blockIdx.y], (size_t)blockIdx.x * blockDim.x + threadIdx.x, 0);
+  run_pheromone(insts[blockIdx.y], blockIdx.x * blockDim.x + threadIdx.x, 0);
 }
 
 // blockIdx.z = instance; instances without verification, and tours or

@@ -49,6 +49,7 @@ enum : int32_t {
 //   cnt_acc   int64 [A][12]      the same summed over all iterations
 struct Inst {
   int32_t n, k, bl, A, m;
+  int32_t ks;         // k rounded up to a multiple of 4: slots of a source-ordered row
   int32_t m_hi;       // calc_num_new_edges() range top (<= m: the constant m)
   int32_t verify;     // 1: each iteration recomputes and checks tour lengths
   int32_t lcap;       // capacity of the LDS part of an ant's work queue
@@ -75,13 +76,13 @@ struct Inst {
   int2 *src_adj;      // [n] (successor, predecessor) of each city in the source
   // Candidate rows in SOURCE order (row p = candidates of the city at source
   // position p), rewritten by the pheromone kernel every iteration; laid out
-  // by srow() in blocks of 64 positions:
-  int32_t *scl;       // candidate city
+  // by srow() in blocks of 64 positions, ks slots per row (those past k hold
+  // weight 0 and the row's own position):
   float *sw;          // tau * eta (Eq. (1) weight)
   int32_t *ssp;       // source position of the candidate
-  int32_t *sd;        // cost of the candidate edge
   int32_t *src_d;     // [n] cost of the source edge from position i to i + 1
   int2 *src_xy;       // [n] coordinates of the city at source position i
+  int4 *sbox;         // [(n + 31) / 32] bounding box of source positions 32 i ..
   int32_t *routes, *pos, *ring;
   int2 *rxy;          // [A][n] coordinates of routes[a][p] (tour order)
   int64_t *lens, *cnt, *cnt_acc;

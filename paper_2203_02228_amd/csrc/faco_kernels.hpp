@@ -89,8 +89,9 @@ FACO_DEV int wrap_off(int q, int off, int n) {
 // ===================================================================== //
 constexpr int kMaxTeam = 8;
 enum TeamOp {
-  OP_EXIT, OP_WINDOW, OP_SWEEP, OP_COPY, OP_NEAREST, OP_OROPT, OP_SEGPERM, OP_SEGMAT, OP_SEARCH
+  OP_EXIT, OP_WINDOW, OP_SWEEP, OP_COPY, OP_NEAREST, OP_NEAREST_LABEL, OP_OROPT, OP_SEGPERM, OP_SEGMAT, OP_SEARCH
 };
+constexpr int kDraws = 1024;     // a power of two
 constexpr int kDescWords = 36;  // a wave's move record in the team local search
 struct TeamLds {
   int op;
@@ -102,6 +103,7 @@ struct TeamLds {
   int64_t ub[kMaxTeam];          // nearest: per-wave bounds
   int cities[kMaxTeam * kWave];  // sweep: the batch of cities to test
   int disp[4];                   // persistent batches: the next task
+  float draws[kDraws];           // roulette draws of the coming steps, by step
   int64_t okey[kMaxTeam][4];     // Or-opt: per-wave maxima of each listed city
   union {
     int orx[14][kWave];          // segment lists' Or-opt: the leader's loaded neighbourhoods
@@ -133,740 +135,7 @@ FACO_DEV void team_post(TeamLds *tl, int op, int a0 = 0, int a1 = 0, int a2 = 0,
 }
 FACO_DEV int team_arg(const TeamLds *tl, int i) { return uniform_i(tl->arg[i]); }
 
-// ===================================================================== //
-// Backup list, then the nearest unvisited city (when no candidate of u is
-// unvisited).  Uniform result.
-// ===================================================================== //
-// Nearest unvisited city to u by (squared distance, original number): lane l
-// of wave w scans bitmap words w * 64 + l, + 64 TW, ...; fully visited words
-// and words whose bounding box lies beyond a bound are skipped.  Each wave
-// leaves its (distance, city) minimum in LDS (TW > 1).
-template <int TW>
-FACO_DEV void nearest_part(const Inst &I, int u, int w, const uint32_t *vis, TeamLds *tl,
-                           int64_t &md, int &mj) {
-  const int lane = lane_id();
-  const int2 xu = I.xy[u];
-  const int W = (I.n + 31) >> 5;
-  auto free_word = [&](int wi) -> uint32_t {
-    if (wi >= W) return 0u;
-    uint32_t f = ~vis[wi];
-    const int rem = I.n - wi * 32;
-    if (rem < 32) f &= (1u << rem) - 1u;
-    return f;
-  };
-  // A bound first: the nearest of the first unvisited cities of the TW 64
-  // bitmap words around u's (labels follow a space-filling curve, so these
-  // are close).  A word whose cities' bounding box lies farther than the
-  // bound cannot hold the nearest city (nor one tied with it) and is skipped.
-  int64_t ub = INT64_MAX;
-  {
-    constexpr int span = TW * kWave;
-    int lo = (u >> 5) - span / 2;
-    lo = lo > W - span ? W - span : lo;
-    lo = lo < 0 ? 0 : lo;
-    const int wi = lo + w * kWave + lane;
-    const uint32_t f = free_word(wi);
-    if (f) ub = (int64_t)sqd_u64(xu, I.xy[wi * 32 + __builtin_ctz(f)]);
-  }
-  ub = wave_min_i64(ub);
-  if (TW > 1) {
-    if (lane == 0) tl->ub[w] = ub;
-    team_sync();
-    ub = wave_min_i64(lane < TW ? tl->ub[lane] : INT64_MAX);
-  }
-  // distances only; equal distances are settled by original number below.
-  // Lane l of wave w takes words w 64 + l + i TW 64, i = 0, 1, ..., 32 at a
-  // time: their boxes are tested with the loads in flight together, then the
-  // unvisited cities of the kept words are taken kNearBatch at a time, so that
-  // their coordinate loads are in flight together too.
-  constexpr int kNearBatch = 8;
-  constexpr int stride = TW * kWave;
-  int64_t bd = INT64_MAX;
-  int bj = 0x7fffffff;
-  bool tie = false;
-  for (int g0 = w * kWave + lane; g0 < W; g0 += 32 * stride) {
-    uint32_t keep = 0u;
-    for (int k0 = 0; k0 < 32; k0 += 8) {
-      int4 bx[8];
-      bool has[8];
-#pragma unroll
-      for (int k = 0; k < 8; ++k) {
-        const int wk = g0 + (k0 + k) * stride;
-        has[k] = free_word(wk) != 0u;
-        bx[k] = has[k] ? I.wbox[wk] : make_int4(0, 0, 0, 0);
-      }
-#pragma unroll
-      for (int k = 0; k < 8; ++k) {
-        if (has[k]) {
-          const int64_t dx = xu.x < bx[k].x ? (int64_t)bx[k].x - xu.x
-                                            : (xu.x > bx[k].z ? (int64_t)xu.x - bx[k].z : 0);
-          const int64_t dy = xu.y < bx[k].y ? (int64_t)bx[k].y - xu.y
-                                            : (xu.y > bx[k].w ? (int64_t)xu.y - bx[k].w : 0);
-          if (dx * dx + dy * dy <= ub) keep |= 1u << (k0 + k);
-        }
-      }
-      if (g0 + (k0 + 8) * stride >= W) break;
-    }
-    int wi = 0;
-    uint32_t fb = 0u;
-    for (;;) {
-      int jb[kNearBatch];
-      bool vb[kNearBatch];
-#pragma unroll
-      for (int k = 0; k < kNearBatch; ++k) {
-        while (fb == 0u && keep != 0u) {
-          wi = g0 + __builtin_ctz(keep) * stride;
-          keep &= keep - 1u;
-          fb = free_word(wi);
-        }
-        vb[k] = fb != 0u;
-        jb[k] = vb[k] ? wi * 32 + __builtin_ctz(fb) : u;
-        fb &= fb - 1u;
-      }
-      if (!vb[0]) break;
-      int2 xb[kNearBatch];
-#pragma unroll
-      for (int k = 0; k < kNearBatch; ++k) xb[k] = I.xy[jb[k]];
-#pragma unroll
-      for (int k = 0; k < kNearBatch; ++k) {
-        if (vb[k]) {
-          const int64_t d = (int64_t)sqd_u64(xu, xb[k]);
-          if (d < bd) {
-            bd = d;
-            bj = jb[k];
-            tie = false;
-          } else if (d == bd) {
-            tie = true;
-          }
-        }
-      }
-    }
-  }
-  md = wave_min_i64(bd);
-  int mo = 0x7fffffff;
-  mj = 0x7fffffff;
-  if (md != INT64_MAX) {
-    const uint64_t at = ballot(bd == md);
-    if (__builtin_popcountll(at) == 1 && !ballot(bd == md && tie)) {
-      mj = readlane_i(bj, ctz64(at));
-      mo = uniform_i(I.orig_of[mj]);
-    } else {
-      // several cities at distance md: the smallest original number
-      int bo = 0x7fffffff, bj2 = 0x7fffffff;
-      for (int wi = w * kWave + lane; wi < W; wi += TW * kWave) {
-        uint32_t free_bits = ~vis[wi];
-        const int rem = I.n - wi * 32;
-        if (rem < 32) free_bits &= (1u << rem) - 1u;
-        while (free_bits) {
-          const int j = wi * 32 + __builtin_ctz(free_bits);
-          free_bits &= free_bits - 1;
-          if ((int64_t)sqd_u64(xu, I.xy[j]) == md) {
-            const int o = I.orig_of[j];
-            if (o < bo) {
-              bo = o;
-              bj2 = j;
-            }
-          }
-        }
-      }
-      mo = wave_min_i32(bo);
-      mj = wave_min_i32(bo == mo ? bj2 : 0x7fffffff);
-    }
-  }
-  if (TW > 1 && lane == 0) {
-    tl->part[w] = md;
-    tl->f[w] = mo;
-    tl->f[kMaxTeam + w] = mj;
-  }
-}
-
-template <int TW>
-FACO_DEV int select_fallback(const Inst &I, int u, const uint32_t *vis, TeamLds *tl,
-                             LaneCounters &cnt) {
-  const int lane = lane_id();
-  int b = 0;
-  bool bu = false;
-  if (lane < I.bl) {
-    b = I.bll[(size_t)u * (size_t)I.bl + lane];
-    bu = !bit_get(vis, b);
-  }
-  const uint64_t bm = ballot(bu);
-  if (bm) {
-    cnt[CNT_BACKUP]++;
-    return readlane_i(b, ctz64(bm));
-  }
-  // best heuristic value = nearest unvisited city, ties by smaller original number
-  cnt[CNT_FALLBACK]++;
-  int64_t md;
-  int mj;
-  if (TW == 1) {
-    nearest_part<1>(I, u, 0, vis, tl, md, mj);
-    return mj;
-  }
-  team_post(tl, OP_NEAREST, u);
-  nearest_part<TW>(I, u, 0, vis, tl, md, mj);
-  team_sync();
-  const int64_t d = lane < TW ? tl->part[lane] : INT64_MAX;
-  const int o = lane < TW ? tl->f[lane] : 0x7fffffff;
-  const int j = lane < TW ? tl->f[kMaxTeam + lane] : 0x7fffffff;
-  const int64_t dmin = wave_min_i64(d);
-  const int omin = wave_min_i32(d == dmin ? o : 0x7fffffff);
-  return uniform_i(wave_min_i32(d == dmin && o == omin ? j : 0x7fffffff));
-}
-
-// Greedy step of the nearest-neighbour tour: first unvisited candidate
-// (lists are sorted by distance), else the fallback chain.  dv = its cost.
-template <int TW>
-FACO_DEV int select_greedy(const Inst &I, int u, const uint32_t *vis, TeamLds *tl, int &dv,
-                           LaneCounters &cnt) {
-  const int K = I.k, lane = lane_id();
-  const size_t row = (size_t)u * (size_t)K;
-  const bool act = lane < K;
-  const int cand = act ? I.cl[row + lane] : 0;
-  const int cd = act ? I.cl_d[row + lane] : 0;
-  const uint64_t um = ballot(act && !bit_get(vis, cand));
-  if (um) {
-    const int s = ctz64(um);
-    dv = readlane_i(cd, s);
-    return readlane_i(cand, s);
-  }
-  const int v = select_fallback<TW>(I, u, vis, tl, cnt);
-  dv = cost(I.xy[u], I.xy[v]);
-  return v;
-}
-
-// ===================================================================== //
-// Copy-from-source (Alg. 2, reading: forward from v while unvisited, else
-// backward).  The first probe looks 64 positions both ways at once; later
-// rounds take 256 positions per wave (64 TW * 4 per round for a team).
-// Edge costs come from the per-iteration source edge table.  Returns the
-// count; u/pu become the last appended city and its source position.
-// ===================================================================== //
-struct CopyOut {
-  int app;      // cities appended
-  int last;     // the last of them (-1: none)
-  int64_t sum;  // their edge costs
-};
-
-// Rounds from source position pcur in direction dir, appending at k.  A
-// round's cities lie past every earlier round's (the walk stops before it
-// could wrap onto them), so a round reads no visited bit another wave of the
-// same round sets.  The per-wave stops of consecutive rounds use alternate
-// LDS slots, so one barrier per round suffices.
-template <int TW>
-FACO_DEV void copy_rounds(const Inst &I, int pcur, int dir, int k, int w, TeamLds *tl,
-                          uint32_t *vis, int32_t *route, int32_t *pos, int2 *rxy,
-                          CopyOut &o) {
-  const int n = I.n, lane = lane_id();
-  constexpr int RW = 4 * kWave;  // positions per wave and round
-  int64_t dsum = 0;
-  int app = 0, last = -1;
-  for (int r = 0;; ++r) {
-    int cc[4], dd[4];
-    int2 cx[4];
-    bool vc[4];
-#pragma unroll
-    for (int h = 0; h < 4; ++h) {
-      const int q = wrap_off(pcur, dir * (w * RW + h * kWave + lane + 1), n);
-      cc[h] = I.src_route[q];
-      cx[h] = I.src_xy[q];
-      dd[h] = I.src_d[dir > 0 ? (q == 0 ? n - 1 : q - 1) : q];
-    }
-#pragma unroll
-    for (int h = 0; h < 4; ++h) vc[h] = bit_get(vis, cc[h]);
-    int jj = RW;
-#pragma unroll
-    for (int h = 3; h >= 0; --h) {
-      const uint64_t m = ballot(vc[h]);
-      if (m) jj = h * kWave + ctz64(m);
-    }
-    int J;
-    if (TW > 1) {
-      int *f = tl->f + (r & 1) * kMaxTeam;
-      if (lane == 0) f[w] = jj < RW ? w * RW + jj : TW * RW;
-      team_sync();
-      J = uniform_i(wave_min_i32(lane < TW ? f[lane] : 0x7fffffff));
-    } else {
-      J = jj;
-    }
-#pragma unroll
-    for (int h = 0; h < 4; ++h) {
-      const int idx = w * RW + h * kWave + lane;
-      if (idx < J) {
-        route[k + idx] = cc[h];
-        pos[cc[h]] = k + idx;
-        rxy[k + idx] = cx[h];
-        bit_set(vis, cc[h]);
-        dsum += dd[h];
-      }
-      if (idx == J - 1) {
-        if (TW > 1)
-          tl->res[0] = cc[h];
-        else
-          last = cc[h];
-      }
-    }
-    if (TW == 1 && J > 0) last = readlane_i(last, (J - 1) & (kWave - 1));
-    app += J;
-    k += J;
-    pcur = wrapn(pcur + dir * J, n);
-    if (J < TW * RW) break;
-  }
-  o.app = app;
-  o.last = last;
-  o.sum = wave_sum_i64(dsum);
-  if (TW > 1 && lane == 0) tl->part[w] = o.sum;
-}
-
-template <int TW>
-FACO_DEV int copy_from(const Inst &I, int pv, int &k, int &u, int &pu, int64_t &len,
-                       TeamLds *tl, int32_t *route, int32_t *pos, int2 *rxy, uint32_t *vis) {
-  const int n = I.n, lane = lane_id();
-  const int qf = wrap_off(pv, lane + 1, n), qb = wrap_off(pv, -lane - 1, n);
-  const int cf = I.src_route[qf], cb = I.src_route[qb];
-  const int2 xf = I.src_xy[qf], xb = I.src_xy[qb];
-  const int df = I.src_d[qf == 0 ? n - 1 : qf - 1], db = I.src_d[qb];
-  const uint64_t mf = ballot(bit_get(vis, cf));
-  const int jf = mf ? ctz64(mf) : kWave;
-  int dir, j, c, d;
-  int2 cxy;
-  if (jf > 0) {
-    dir = 1; j = jf; c = cf; d = df; cxy = xf;
-  } else {
-    const uint64_t mb = ballot(bit_get(vis, cb));
-    dir = -1; j = mb ? ctz64(mb) : kWave; c = cb; d = db; cxy = xb;
-  }
-  if (j == 0) return 0;
-  if (lane < j) {
-    route[k + lane] = c;
-    pos[c] = k + lane;
-    rxy[k + lane] = cxy;
-    bit_set(vis, c);
-  }
-  len += wave_sum_i64(lane < j ? (int64_t)d : 0);
-  u = readlane_i(c, j - 1);
-  k += j;
-  const int pcur = wrap_off(pv, dir * j, n);
-  if (j < kWave) {
-    pu = pcur;
-    return j;
-  }
-  CopyOut o;
-  if (TW > 1) {
-    team_post(tl, OP_COPY, pcur, dir, k);
-    copy_rounds<TW>(I, pcur, dir, k, 0, tl, vis, route, pos, rxy, o);
-    team_sync();
-    o.app = uniform_i(o.app);
-    o.sum = wave_sum_i64(lane < TW ? tl->part[lane] : 0);
-    o.last = o.app > 0 ? uniform_i(tl->res[0]) : -1;
-  } else {
-    wave_fence();
-    copy_rounds<1>(I, pcur, dir, k, 0, tl, vis, route, pos, rxy, o);
-  }
-  len += o.sum;
-  if (o.app > 0) u = o.last;
-  k += o.app;
-  pu = wrapn(pcur + dir * o.app, n);
-  return j + o.app;
-}
-
-// ===================================================================== //
-// Speculative source-following window.  Lane i evaluates ACO step `step + i`
-// as if the ant had followed the source in direction dir for the previous i
-// steps: its current city is q_i (q_0 = u at source position pu), its
-// visited set V + {q_1..q_i} (V in LDS, the q's recognised by their source
-// positions).  The first lane whose choice is not q_{i+1} ends the window;
-// its choice is exact because every earlier lane confirmed the assumption.
-// Same draws, same weights, same order as the one-step-at-a-time rule.
-// Output: acc = steps that followed the source; then, unless the window ran
-// out (v = -2), the decision of step `step + acc`: v with its cost dv and
-// source position pv, or v = -1 when no candidate is unvisited.
-// ===================================================================== //
-struct Draws {
-  uint64_t base;  // lane j holds the roulette draw of step base + j
-  float u;
-  bool valid;
-};
-
-struct WinOut {
-  int acc;        // steps that followed the source
-  int v, dv, pv;  // decision of step `step + acc` (v = -2: window ran out)
-  int lastq;      // city reached after the accepted steps
-  int64_t srcsum; // their edge costs
-};
-
-// Wave w of a team evaluates steps step + 64 w + lane (TW = 1: lanes only).
-// The accepted steps are appended to the tour here (route, pos, rxy and the
-// visited bits), by the wave that evaluated them.
-template <int KT, int TW>
-FACO_DEV void window_part(const Inst &I, uint64_t t, uint64_t ant, uint64_t step, int u,
-                          int pu, int dir, int k, int maxw, int w, TeamLds *tl,
-                          uint32_t *vis, int32_t *route, int32_t *pos, int2 *rxy, Draws &D,
-                          WinOut &o, int round = 0) {
-  const int n = I.n, K = I.k, lane = lane_id();
-  const int g = w * kWave + lane;
-  o.v = -2;
-  o.dv = 0;
-  o.pv = 0;
-  o.lastq = u;
-  o.srcsum = 0;
-  // every load below is addressed by source position: one round trip
-  const int rpos = wrap_off(pu, dir * g, n);      // position of q_g
-  const int qpos = wrap_off(pu, dir * (g + 1), n);
-  const int qn = I.src_route[qpos];                // q_{g+1}
-  const int2 qxy = I.src_xy[qpos];
-  const int ed = I.src_d[dir > 0 ? rpos : qpos];   // cost q_g -> q_{g+1}
-  const size_t row = srow(rpos, 0, K);
-  int c[KT], sp[KT], cd[KT];
-  float wt[KT];
-#pragma unroll
-  for (int s = 0; s < KT; ++s) {
-    if (s < K) {
-      c[s] = I.scl[row + 64 * s];
-      wt[s] = I.sw[row + 64 * s];
-      sp[s] = I.ssp[row + 64 * s];
-      cd[s] = I.sd[row + 64 * s];
-    }
-  }
-  D.u = unit24(philox_word0(I.seed, t, ant, step + (uint64_t)g, kPurposeRoulette));
-  D.base = step + (uint64_t)(w * kWave);
-  D.valid = true;
-  const float U = D.u;
-  float P[KT];
-  float total = 0.0f;
-  int last = -1;
-#pragma unroll
-  for (int s = 0; s < KT; ++s) {
-    if (s < K) {
-      const int off = dir > 0 ? sp[s] - pu : pu - sp[s];
-      const int offw = off < 0 ? off + n : off;
-      const bool visited = bit_get(vis, c[s]) || (offw >= 1 && offw <= g);
-      if (!visited) {
-        total = total + wt[s];
-        last = s;
-      }
-      P[s] = total;
-    }
-  }
-  const bool special = last < 0;
-  int choice = 0, choice_d = 0, choice_p = 0;
-  if (!special) {
-    const float r = U * total;
-    int sel = -1;
-#pragma unroll
-    for (int s = KT - 1; s >= 0; --s)
-      if (s < K && P[s] > r) sel = s;
-    if (sel < 0) sel = last;
-#pragma unroll
-    for (int s = 0; s < KT; ++s)
-      if (s == sel) {
-        choice = c[s];
-        choice_d = cd[s];
-        choice_p = sp[s];
-      }
-  }
-  int valid = n - k < TW * kWave ? n - k : TW * kWave;  // steps left
-  valid = valid < maxw ? valid : maxw;
-  const bool match = !special && choice == qn && g < valid;
-  const uint64_t mm = ballot(!match);
-  int F = mm ? w * kWave + ctz64(mm) : TW * kWave;
-  if (TW > 1) {
-    int *f = tl->f + (round & 1) * kMaxTeam;
-    if (lane == 0) f[w] = F;
-    team_sync();  // every wave's evaluation is done before any append
-    F = uniform_i(wave_min_i32(lane < TW ? f[lane] : 0x7fffffff));
-  }
-  const int acc = F < valid ? F : valid;
-  if (g < acc) {
-    route[k + g] = qn;
-    pos[qn] = k + g;
-    rxy[k + g] = qxy;
-    bit_set(vis, qn);
-  }
-  const int64_t ssum = wave_sum_i64(g < acc ? (int64_t)ed : 0);
-  o.acc = acc;
-  if (TW == 1) {
-    o.srcsum = ssum;
-    o.lastq = acc > 0 ? readlane_i(qn, acc - 1) : u;
-    if (acc < valid) {
-      if (readlane_i(special ? 1 : 0, acc)) {
-        o.v = -1;
-      } else {
-        o.v = readlane_i(choice, acc);
-        o.dv = readlane_i(choice_d, acc);
-        o.pv = readlane_i(choice_p, acc);
-      }
-    } else {
-      o.v = -2;
-    }
-  } else {
-    // results for the leader, read after the closing barrier
-    o.srcsum = ssum;
-    if (acc > 0 && g == acc - 1) tl->res[0] = qn;
-    if (acc < valid && g == acc) {
-      tl->res[1] = special ? -1 : choice;
-      tl->res[2] = choice_d;
-      tl->res[3] = choice_p;
-    }
-    o.v = acc < valid ? 0 : -2;
-  }
-}
-
-// A team runs up to kWinRounds windows in one command: while a window is
-// followed to its end, the next one starts from where it stopped (every wave
-// derives the new start alike; the last followed city comes through LDS).
-// Per-wave partial sums of the followed edges end in tl->part.
-constexpr int kWinRounds = 16;
-template <int KT, int TW>
-FACO_DEV void window_rounds(const Inst &I, uint64_t t, uint64_t ant, uint64_t step, int u,
-                            int pu, int dir, int k, int maxw, int w, TeamLds *tl,
-                            uint32_t *vis, int32_t *route, int32_t *pos, int2 *rxy, Draws &D,
-                            WinOut &o) {
-  const int n = I.n;
-  int total = 0;
-  int64_t sum = 0;
-  for (int r = 0;; ++r) {
-    WinOut q;
-    window_part<KT, TW>(I, t, ant, step, u, pu, dir, k, maxw, w, tl, vis, route, pos, rxy, D,
-                        q, r);
-    const int acc = uniform_i(q.acc);
-    total += acc;
-    sum += q.srcsum;
-    int valid = n - k < TW * kWave ? n - k : TW * kWave;
-    valid = valid < maxw ? valid : maxw;
-    team_sync();  // this window's appends and results are visible
-    if (acc < valid || r + 1 >= kWinRounds || k + acc >= n) {
-      o = q;
-      break;
-    }
-    u = uniform_i(tl->res[0]);
-    pu = wrap_off(pu, dir * acc, n);
-    k += acc;
-    step += (uint64_t)acc;
-  }
-  o.acc = total;
-  if (lane_id() == 0) tl->part[w] = sum;
-}
-
-// Leader side of a window (TW > 1: posts it, takes wave 0's share, collects).
-template <int KT, int TW>
-FACO_DEV WinOut team_window(const Inst &I, uint64_t t, uint64_t ant, uint64_t step, int u,
-                            int pu, int dir, int k, int maxw, TeamLds *tl, uint32_t *vis,
-                            int32_t *route, int32_t *pos, int2 *rxy, Draws &D) {
-  WinOut o;
-  if (TW > 1) {
-    if (lane_id() == 0) {
-      tl->arg64[0] = t;
-      tl->arg64[1] = step;
-    }
-    team_post(tl, OP_WINDOW, u, pu, dir, k, maxw);
-  }
-  if (TW > 1)
-    window_rounds<KT, TW>(I, t, ant, step, u, pu, dir, k, maxw, 0, tl, vis, route, pos, rxy, D,
-                          o);
-  else
-    window_part<KT, TW>(I, t, ant, step, u, pu, dir, k, maxw, 0, tl, vis, route, pos, rxy, D,
-                        o);
-  if (TW > 1) {
-    team_sync();
-    o.acc = uniform_i(o.acc);
-    o.srcsum = wave_sum_i64(lane_id() < TW ? tl->part[lane_id()] : 0);
-    o.lastq = o.acc > 0 ? uniform_i(tl->res[0]) : u;
-    if (uniform_i(o.v) == 0) {
-      o.v = uniform_i(tl->res[1]);
-      o.dv = uniform_i(tl->res[2]);
-      o.pv = uniform_i(tl->res[3]);
-    } else {
-      o.v = -2;
-    }
-  }
-  return o;
-}
-
-// One ACO step from the city at source position pu, lane s = candidate slot
-// s (used once new_edges >= m, when every step is followed by a copy).
-// v = -1 when no candidate is unvisited.
-FACO_DEV int one_step(const Inst &I, uint64_t t, uint64_t ant, uint64_t step, int pu,
-                      const uint32_t *vis, Draws &D, int &dv, int &pv) {
-  const int n = I.n, K = I.k, lane = lane_id();
-  (void)n;
-  const bool act = lane < K;
-  const size_t row = srow(pu, act ? lane : 0, K);
-  const int c = act ? I.scl[row] : 0;
-  const float w = act ? I.sw[row] : 0.0f;
-  const int sp = act ? I.ssp[row] : 0;
-  const int d = act ? I.sd[row] : 0;
-  const bool unv = act && !bit_get(vis, c);
-  const uint64_t um = ballot(unv);
-  if (!um) return -1;
-  if (!(D.valid && step >= D.base && step < D.base + kWave)) {
-    D.u = unit24(philox_word0(I.seed, t, ant, step + (uint64_t)lane, kPurposeRoulette));
-    D.base = step;
-    D.valid = true;
-  }
-  const float U = readlane_f(D.u, (int)(step - D.base));
-  const float wv = unv ? w : 0.0f;
-  // cumulative sum in slot order: lane s holds fl(...fl(w_0 + w_1)... + w_s)
-  float P = 0.0f;
-  for (int j = 0; j < K; ++j) {
-    const float wj = readlane_f(wv, j);
-    if (j <= lane) P = P + wj;
-  }
-  const float r = U * readlane_f(P, K - 1);
-  const uint64_t sm = ballot(act && P > r);
-  const int s = sm ? ctz64(sm) : msb64(um);
-  dv = readlane_i(d, s);
-  pv = readlane_i(sp, s);
-  return readlane_i(c, s);
-}
-
-// ===================================================================== //
-// Focused construction (Alg. 2 inner loop).  greedy: nearest-neighbour tour
-// from city 0 (initial solution), no source, no copy.
-// The checklist is written into ring[0..nchk) with its LDS bits set in inq.
-// ===================================================================== //
-FACO_DEV void append_city(const Inst &I, int v, int k, int32_t *route, int32_t *pos,
-                          int2 *rxy, uint32_t *vis) {
-  if (lane_id() == 0) {
-    route[k] = v;
-    pos[v] = k;
-    rxy[k] = I.xy[v];
-    bit_set(vis, v);
-  }
-}
-
-// tk: [5] speculative windows, [6] one-step calls, [7] copies, [8..10] their
-// ticks, [11] ticks in backup/nearest-city choices
-template <int KT, int TW>
-FACO_DEV int64_t construct(const Inst &I, uint64_t t, int ant, bool greedy,
-                           int32_t *route, int32_t *pos, int2 *rxy, int32_t *ring,
-                           uint32_t *vis, uint32_t *inq, TeamLds *tl, int W, int &nchk,
-                           LaneCounters &cnt, LaneCounters &tk) {
-  const int n = I.n, lane = lane_id();
-  for (int w = lane; w < W; w += kWave) {
-    vis[w] = 0u;
-    inq[w] = 0u;
-  }
-  wave_fence();
-  // start: city 0 for the greedy tour, else a uniform draw (original numbers)
-  const int r0 = uniform_i(
-      I.int_of[greedy ? 0
-                      : uniform_node(philox_word0(I.seed, t, (uint64_t)ant, 0, kPurposeStart),
-                                     n)]);
-  int u = r0;
-  append_city(I, u, 0, route, pos, rxy, vis);
-  // calc_num_new_edges() (Alg. 2): the constant min_new_edges, or this ant's
-  // uniform draw from [min_new_edges, min_new_edges_max]
-  int m = I.m;
-  if (!greedy && I.m_hi > I.m)
-    m += (int)__umul64hi(philox_word0(I.seed, t, (uint64_t)ant, 0, kPurposeNewEdges),
-                         (uint64_t)(I.m_hi - I.m) + 1u);
-  m = uniform_i(m);
-  int k = 1, new_edges = 0;
-  nchk = 0;
-  int64_t len = 0;
-  uint64_t step = 0;
-  if (greedy) {
-    while (k < n) {
-      int dv;
-      const int v = uniform_i(select_greedy<TW>(I, u, vis, tl, dv, cnt));
-      ++step;
-      len += dv;
-      append_city(I, v, k, route, pos, rxy, vis);
-      k = uniform_i(k + 1);
-      u = v;
-    }
-  } else {
-    int pu = uniform_i(I.src_pos[u]);
-    int dir = 1;
-    Draws D;
-    D.base = 0;
-    D.u = 0.0f;
-    D.valid = false;
-    while (k < n) {
-      // Once new_edges >= m every ACO step is followed by a copy, so the
-      // window is one step wide.
-      // loop state is wave-uniform; keep it in scalar registers so that the
-      // team barriers below sit in scalar control flow
-      k = uniform_i(k);
-      new_edges = uniform_i(new_edges);
-      u = uniform_i(u);
-      pu = uniform_i(pu);
-      dir = uniform_i(dir);
-      step = uniform_u64(step);
-      const int maxw = new_edges >= m ? 1 : TW * kWave;
-      int v, dv = 0, pv = 0;
-      const int64_t c0 = fine_ticks();
-      if (maxw == 1) {
-        v = one_step(I, t, (uint64_t)ant, step, pu, vis, D, dv, pv);
-        tk[6]++;
-        tk[9] += fine_ticks() - c0;
-      } else {
-        // accepted steps follow the source: q_1..q_acc appended at k..k+acc-1
-        const WinOut o = team_window<KT, TW>(I, t, (uint64_t)ant, step, u, pu, dir, k, maxw,
-                                             tl, vis, route, pos, rxy, D);
-        tk[5]++;
-        tk[8] += fine_ticks() - c0;
-        const int acc = uniform_i(o.acc);
-        v = uniform_i(o.v);
-        dv = uniform_i(o.dv);
-        pv = uniform_i(o.pv);
-        if (acc > 0) {
-          k += acc;
-          step += acc;
-          len += o.srcsum;
-          pu = wrap_off(pu, dir * acc, n);
-          u = uniform_i(o.lastq);
-        }
-        wave_fence();
-      }
-      if (v == -2) {
-        // the whole window followed the source; no step off the path
-        v = u;
-        pv = pu;
-      } else {
-        if (v == -1) {
-          const int64_t c1 = fine_ticks();
-          v = uniform_i(select_fallback<TW>(I, u, vis, tl, cnt));
-          dv = uniform_i(cost(I.xy[u], I.xy[v]));
-          pv = uniform_i(I.src_pos[v]);
-          tk[11] += fine_ticks() - c1;
-        }
-        ++step;
-        len += dv;
-        append_city(I, v, k, route, pos, rxy, vis);
-        ++k;
-        const int fwd = pu + 1 == n ? 0 : pu + 1, bwd = pu == 0 ? n - 1 : pu - 1;
-        if (pv != fwd && pv != bwd) {
-          ++new_edges;
-          if (lane == 0) {
-            ring[nchk] = v;
-            bit_set(inq, v);
-          }
-          ++nchk;
-        }
-        dir = pv == bwd ? -1 : 1;
-      }
-      u = uniform_i(v);
-      pu = uniform_i(pv);
-      new_edges = uniform_i(new_edges);
-      k = uniform_i(k);
-      dir = uniform_i(dir);
-      if (new_edges >= m && k < n) {
-        const int64_t c2 = fine_ticks();
-        const int app = copy_from<TW>(I, pv, k, u, pu, len, tl, route, pos, rxy, vis);
-        cnt[CNT_COPIED] += app;
-        tk[7]++;
-        tk[10] += fine_ticks() - c2;
-      }
-    }
-  }
-  len += cost(I.xy[u], I.xy[r0]);
-  cnt[CNT_ACO_STEPS] += (int64_t)step;
-  cnt[CNT_NEW_EDGES] += new_edges;
-  wave_fence();
-  return len;
-}
+#include "faco_construct.hpp"
 
 // ===================================================================== //
 // Local search (Alg. 3 + Or-opt + sweep)
@@ -1939,7 +1208,6 @@ FACO_DEV int64_t local_search(const Inst &I, uint32_t flags, int32_t *route,
 template <int KT, int TW, bool SEG>
 FACO_DEV int team_helper(const Inst &I, int ant, int w, TeamLds *tl, uint32_t *vis,
                           uint32_t *ord, int32_t *route, int32_t *pos, int2 *rxy, int4 *rec) {
-  Draws D;
   // a segment-list move's record whose cities this wave labels after the move
   int rl_h = -1, rl_lo = 0, rl_hi = -1;
   SegT rl_T;
@@ -1953,18 +1221,21 @@ FACO_DEV int team_helper(const Inst &I, int ant, int w, TeamLds *tl, uint32_t *v
     if (op == OP_EXIT || op == OP_SEARCH) return op;
     if (op == OP_WINDOW) {
       WinOut o;
-      window_rounds<KT, TW>(I, uniform_u64(tl->arg64[0]), (uint64_t)ant,
-                            uniform_u64(tl->arg64[1]), team_arg(tl, 0), team_arg(tl, 1),
-                            team_arg(tl, 2), team_arg(tl, 3), team_arg(tl, 4), w, tl, vis,
-                            route, pos, rxy, D, o);
+      int have = team_arg(tl, 4);
+      window_rounds<KT, TW>(I, uniform_u64(tl->arg64[0]), (uint64_t)ant, team_arg(tl, 3),
+                            team_arg(tl, 0), team_arg(tl, 1), team_arg(tl, 2), w, have, tl, vis,
+                            route, pos, rxy, o);
     } else if (op == OP_COPY) {
-      CopyOut o;
-      copy_rounds<TW>(I, team_arg(tl, 0), team_arg(tl, 1), team_arg(tl, 2), w, tl, vis, route,
-                      pos, rxy, o);
-    } else if (op == OP_NEAREST) {
+      const int64_t sum = copy_part<TW>(I, team_arg(tl, 0), team_arg(tl, 1), team_arg(tl, 2),
+                                        team_arg(tl, 3), w, route, pos, rxy);
+      if (lane_id() == 0) tl->part[w] = sum;
+    } else if (op == OP_NEAREST || op == OP_NEAREST_LABEL) {
       int64_t md;
       int mj;
-      nearest_part<TW>(I, team_arg(tl, 0), w, vis, tl, md, mj);
+      if (op == OP_NEAREST)
+        nearest_part<true, TW>(I, team_arg(tl, 0), w, vis, tl, md, mj);
+      else
+        nearest_part<false, TW>(I, team_arg(tl, 0), w, vis, tl, md, mj);
     } else if (SEG && op == OP_SWEEP) {
       sweep_part<KT, TW>(I, (uint32_t)team_arg(tl, 1), team_arg(tl, 0), w, tl, ord,
                          seg_view(I, ant, rec, uniform_i(tl->sgs[0]), uniform_i(tl->sgs[1]),
@@ -2099,10 +1370,10 @@ FACO_DEV void run_ant(const Inst &I, int ant, int mode, uint32_t *lds) {
     if (team_helper<KT, TW, SEG>(I, ant, w, tl, vis, ord, route, pos, rxy, rec) == OP_EXIT)
       return;
   } else {
-    const uint64_t t = (uint64_t)I.st->iter + 1;
     int nchk = 0;
-    len = construct<KT, TW>(I, t, ant, init, route, pos, rxy, ring, vis, inq, tl, W, nchk, cnt,
-                            tk);
+    len = init ? construct_greedy<TW>(I, route, pos, rxy, vis, inq, tl, W, cnt)
+               : construct<KT, TW>(I, (uint64_t)I.st->iter + 1, ant, route, pos, rxy, ring, vis,
+                                   inq, tl, W, nchk, cnt, tk);
     tk[0] = ticks() - t0;
     flags = search_setup(I, init, W, nchk, ring, vis, inq, ord, Q, cnt);
     if constexpr (SEG || TW == 1) {
@@ -2296,10 +1567,10 @@ template <int TW>
 FACO_DEV void worker_update(const Inst &I, int tid, int nt) {
   if (tid < kWave) run_colony(I);
   if (TW > 1) team_sync(); else wave_fence();
-  for (int i = tid; i < I.n; i += nt) run_source(I, i, 0);
+  for (int i = tid; i - lane_id() < I.n; i += nt) run_source(I, i, 0);
   if (TW > 1) team_sync(); else wave_fence();
-  const size_t slots = (size_t)I.n * (size_t)I.k;
-  for (size_t s = (size_t)tid; s < slots; s += (size_t)nt) run_pheromone(I, s, 0);
+  const uint32_t slots = (uint32_t)I.n * (uint32_t)I.ks;
+  for (uint32_t s = (uint32_t)tid; s < slots; s += (uint32_t)nt) run_pheromone(I, s, 0);
   if (TW > 1) team_sync(); else wave_fence();
 }
 

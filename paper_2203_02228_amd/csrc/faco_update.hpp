@@ -63,12 +63,15 @@ FACO_DEV void run_colony(const Inst &I) {
 
 // Source materialisation: the chosen tour becomes source_solution (route and
 // its inverse), the iteration best becomes the global best when it improved.
-// init: source := global best (before the first iteration).
+// init: source := global best (before the first iteration).  Called with
+// whole waves on 64 consecutive i (a multiple of 64 first), past n too.
 FACO_DEV void run_source(const Inst &I, int i, int init) {
   const int n = I.n;
-  if (i >= n) return;
+  if (i - lane_id() >= n) return;
   const DevState *st = I.st;
-  const int i1 = i + 1 == n ? 0 : i + 1, i0 = i == 0 ? n - 1 : i - 1;
+  const bool valid = i < n;
+  const int ic = valid ? i : n - 1;
+  const int i1 = ic + 1 == n ? 0 : ic + 1, i0 = ic == 0 ? n - 1 : ic - 1;
   const int32_t *from;
   if (init) {
     from = I.gb_route;
@@ -76,21 +79,46 @@ FACO_DEV void run_source(const Inst &I, int i, int init) {
     const int32_t *ibr = ant_route(I, st->ib);
     from = (st->src_gb && !st->improved) ? I.gb_route : ibr;
   }
-  const int node = from[i], next = from[i1], prev = from[i0];
-  if (!init && st->improved) I.gb_route[i] = node;
-  I.src_route[i] = node;
-  I.src_pos[node] = i;
-  I.src_adj[node] = make_int2(next, prev);
+  const int node = from[ic], next = from[i1], prev = from[i0];
   const int2 xn = I.xy[node];
-  I.src_xy[i] = xn;
-  I.src_d[i] = cost(xn, I.xy[next]);
+  if (valid) {
+    if (!init && st->improved) I.gb_route[i] = node;
+    I.src_route[i] = node;
+    I.src_pos[node] = i;
+    I.src_adj[node] = make_int2(next, prev);
+    I.src_xy[i] = xn;
+    I.src_d[i] = cost(xn, I.xy[next]);
+  }
+  // bounding box of each half wave's 32 positions (those past n repeat the
+  // last city)
+  int4 b = make_int4(xn.x, xn.y, xn.x, xn.y);
+#pragma unroll
+  for (int o = 1; o < 32; o <<= 1) {
+    b.x = min(b.x, __shfl_xor(b.x, o));
+    b.y = min(b.y, __shfl_xor(b.y, o));
+    b.z = max(b.z, __shfl_xor(b.z, o));
+    b.w = max(b.w, __shfl_xor(b.w, o));
+  }
+  if (valid && (i & 31) == 0) I.sbox[i >> 5] = b;
 }
 
 // Eq. (2) with the deposit on the source edges: tau' = clamp(rho tau + delta
 // [edge in source]).  init: tau = tau_max everywhere.
-FACO_DEV void run_pheromone(const Inst &I, size_t idx, int init) {
-  const int n = I.n, K = I.k;
-  if (idx >= (size_t)n * (size_t)K) return;
+// slot: (city, slot of its padded source-ordered row).
+FACO_DEV void run_pheromone(const Inst &I, uint32_t slot, int init) {
+  const uint32_t n = (uint32_t)I.n, K = (uint32_t)I.k, KS = (uint32_t)I.ks;
+  if (slot >= n * KS) return;
+  const uint32_t i = slot / KS, s = slot - i * KS;
+  // candidate row of city i moved to row src_pos(i), read by the next
+  // construction: its Eq. (1) weight and the candidate's source position
+  const int pi = I.src_pos[i];
+  const size_t o = srow(pi, (int)s, (int)KS);
+  if (s >= K) {
+    I.sw[o] = 0.0f;
+    I.ssp[o] = pi;
+    return;
+  }
+  const uint32_t idx = i * K + s;
   const DevState *st = I.st;
   const float tmin = st->tau_min, tmax = st->tau_max;
   const int j = I.cl[idx];
@@ -98,7 +126,6 @@ FACO_DEV void run_pheromone(const Inst &I, size_t idx, int init) {
   if (init) {
     tnew = tmax;
   } else {
-    const int i = (int)(idx / (size_t)K);
     const int2 adj = I.src_adj[i];
     const float t1 = I.rho * I.tau[idx];
     float t2 = (j == adj.x || j == adj.y) ? t1 + st->delta : t1;
@@ -107,14 +134,8 @@ FACO_DEV void run_pheromone(const Inst &I, size_t idx, int init) {
     tnew = t2;
   }
   I.tau[idx] = tnew;
-  // candidate row of city i moved to row src_pos(i), read by the next
-  // construction: the city, its Eq. (1) weight, source position and cost
-  const int i = (int)(idx / (size_t)K), s = (int)(idx - (size_t)i * K);
-  const size_t o = srow(I.src_pos[i], s, K);
-  I.scl[o] = j;
   I.sw[o] = tnew * I.eta[idx];
   I.ssp[o] = I.src_pos[j];
-  I.sd[o] = I.cl_d[idx];
 }
 
 }  // namespace faco
