@@ -18,6 +18,9 @@ AntBatchFn faco_ant_batch_kernel(int k, int tw);
 // persistent batched ant kernel (all iterations of every instance in one
 // launch; one wave per ant, several per workgroup, or tw waves per ant)
 AntPersistFn faco_ant_persist_kernel(int k, int tw);
+// one sweep of the initial search over all cities
+typedef void (*InitSweepFn)(faco::Inst);
+InitSweepFn faco_init_sweep_kernel(int k);
 // LDS words of the team area ahead of an ant's bitmaps
 int faco_team_lds_words(int tw);
 // ant kernel whose local search runs on segment-list tours (Inst.seg_on)

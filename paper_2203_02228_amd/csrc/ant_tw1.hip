@@ -43,3 +43,12 @@ AntBatchFn faco_ant_batch_kernel(int k, int tw) {
 int faco_team_lds_words(int tw) {
   return tw == 1 ? faco::team_words<1>() : faco::team_words<8>();
 }
+
+InitSweepFn faco_init_sweep_kernel(int k) {
+  if (k <= 4) return faco::init_sweep_kernel<4>;
+  if (k <= 8) return faco::init_sweep_kernel<8>;
+  if (k <= 12) return faco::init_sweep_kernel<12>;
+  if (k <= 16) return faco::init_sweep_kernel<16>;
+  if (k <= 24) return faco::init_sweep_kernel<24>;
+  return faco::init_sweep_kernel<32>;
+}

@@ -351,6 +351,7 @@ extern "C" uint64_t faco_footprint_bytes(int32_t n, const faco_params *p) {
   SegPlan sp;
   if (seg_plan(n, team_waves_for(n, p->n_ants), &sp) == FACO_OK && sp.on)
     b += 2 * align_up(4 * N * A) + 2 * align_up(8 * N * A) + align_up(4 * A);  // segment lists
+  b += align_up(4 * ((N + 31) / 32));      // marks of the initial search's sweeps
   b += 2 * align_up(8 * (A + 1)) + align_up(4 * (A + 1));  // verification
   b += align_up(sizeof(DevState));
   return b;
@@ -445,6 +446,13 @@ static void hilbert_labels(const int32_t *xy, int32_t n, std::vector<int32_t> &o
   }
 }
 
+// Initial searches of at least this many cities run their sweeps as launches
+// over the whole chip.  A sweep by the search's own workgroup costs 57 ns a
+// city (8 waves), a launch and the search's next one about 40 us together:
+// builds of 1500 cities 4.53 against 4.62 ms, of 5000 9.4 against 10.1, of
+// 100 000 173 against 547 (66 sweeps); of 700 both 3.56 ms.
+static const int32_t kChipSweepMin = 1024;
+
 extern "C" int faco_build_instance(const int32_t *xy, int32_t n, const faco_params *p,
                                    void *hip_stream, faco_instance **out) {
   if (!out) return set_err(nullptr, FACO_EINVAL, "out is NULL");
@@ -536,6 +544,7 @@ extern "C" int faco_build_instance(const int32_t *xy, int32_t n, const faco_para
     ALLOC(sgid, int2, N * A);
     ALLOC(sepoch, int32_t, A);
   }
+  ALLOC(marks, uint32_t, (N + 31) / 32);
   ALLOC(vsum, int64_t, A + 1);
   ALLOC(vbad, int32_t, A + 1);
   ALLOC(vout, int64_t, A + 1);
@@ -631,8 +640,29 @@ extern "C" int faco_build_instance(const int32_t *xy, int32_t n, const faco_para
   }
   // initial solution (ant slot 0, flat tour), limits, tau = tau_max, source =
   // global best
-  hipLaunchKernelGGL(faco_ant_kernel(h->k, h->tw), dim3(1), dim3(64 * h->tw), h->lds_init,
-                     h->stream, I, 1);
+  const AntKernelFn initk = faco_ant_kernel(h->k, h->tw);
+  auto launch_init = [&](int mode) {
+    hipLaunchKernelGGL(initk, dim3(1), dim3(64 * h->tw), h->lds_init, h->stream, I, mode);
+  };
+  if (n < kChipSweepMin || (p->ls_flags & FACO_LS_INIT_3OPT)) {
+    launch_init(1);
+  } else {
+    // a launch per sweep; the search's end is looked for every few sweeps
+    // (launches after it return at once).  Every launch before the end makes
+    // at least one of at most n moves.
+    launch_init(2);
+    for (;;) {
+      for (int r = 0; r < 3; ++r) {
+        hipLaunchKernelGGL(faco_init_sweep_kernel(h->k), dim3((unsigned)((n + 255) / 256)),
+                           dim3(256), 0, h->stream, I);
+        launch_init(3);
+      }
+      BTRY(hipGetLastError());
+      BTRY(hipMemcpyAsync(&hs, I.st, sizeof(DevState), hipMemcpyDeviceToHost, h->stream));
+      BTRY(hipStreamSynchronize(h->stream));
+      if (hs.init_done) break;
+    }
+  }
   if (p->ls_flags & FACO_LS_INIT_3OPT) {
     // the initial search with 3-opt, on the nearest-neighbour tour
     const size_t ilds = sizeof(uint32_t) * 2 * ((N + 31) / 32);

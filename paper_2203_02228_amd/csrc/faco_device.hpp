@@ -21,6 +21,11 @@ struct DevState {
   // Faults found on the device (FAULT_* bits; the first one's ant and
   // iteration), and the number of tours the verification kernel has checked.
   int32_t fault, fault_ant;
+  // The initial search between its launches (sweeps in launches of their own):
+  // tour length, moves made, clock at the end of the last launch, whether it
+  // has ended.
+  int64_t init_cur, init_clock;
+  int32_t init_changes, init_done;
   int64_t fault_iter;
   int64_t verified;
 };
@@ -102,6 +107,8 @@ struct Inst {
   int32_t *rsel;      // [A] buffer holding each ant's final tour (0: routes, 1: r2)
   // tour-length verification: partial sums and route faults of the tours
   // being checked (ants 0..A-1, then the global best), the last results
+  uint32_t *marks;    // [(n + 31) / 32] cities (original numbers) a sweep of the
+                      // initial search found improvable; zero between sweeps
   int64_t *vsum;      // [A + 1], zero between verifications
   int32_t *vbad;      // [A + 1], zero between verifications
   int64_t *vout;      // [A + 1] recomputed lengths (-1: not a permutation)

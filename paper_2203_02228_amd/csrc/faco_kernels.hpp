@@ -1021,17 +1021,18 @@ FACO_DEV void record_fault(const Inst &I, int32_t bit, int ant) {
 }
 
 // SEG: the tour is a segment list (SQ); else the flat arrays route, pos, rxy.
+// changes: moves made before (in) and by the end (out).
 template <int KT, int TW, bool SEG>
 FACO_DEV int64_t local_search(const Inst &I, uint32_t flags, int32_t *route,
                               int32_t *pos, int2 *rxy, uint32_t *inq, uint32_t *touched,
                               uint32_t *ord, TeamLds *tl, int W, Queue Q, LaneCounters &cnt,
-                              LaneCounters &tk, int ant, SegState &SQ) {
+                              LaneCounters &tk, int ant, SegState &SQ, int &changes) {
   constexpr int GS = KT <= 16 ? 16 : 32;  // lanes per evaluated city
   constexpr int G = kWave / GS;           // cities evaluated together
   const int n = I.n, lane = lane_id();
   const int grp = lane / GS;
   flags = (uint32_t)uniform_i((int)flags);
-  int changes = 0, changes_at_sweep = -1;
+  int changes_at_sweep = -1;
   int64_t gain = 0;
   // The next round's static loads (its groups' candidate rows and
   // coordinates), issued during this round for the groups it will most
@@ -1282,29 +1283,53 @@ FACO_DEV int team_helper(const Inst &I, int ant, int w, TeamLds *tl, uint32_t *v
 }
 
 // ===================================================================== //
-// One ant: construction + local search.  mode 0: ant `ant` of iteration
-// st->iter + 1.  mode 1: initial solution (nearest neighbour + LS over all
-// cities) written to the global best.
+// One ant: construction + local search.  MODE_ANT: ant `ant` of iteration
+// st->iter + 1.  MODE_INIT: initial solution (nearest neighbour + LS over all
+// cities) written to the global best.  MODE_INIT_FIRST, MODE_INIT_MORE: the
+// same with the sweeps in launches of their own (init_sweep_kernel, the whole
+// chip instead of one workgroup): the first launch searches until no city is
+// listed, each later one lists what the sweep before it marked and goes on;
+// one that finds nothing marked ends the search (DevState.init_done).
 //   lds: [team area][visited W][listed W][sweep order W]
 //        [SEG: segment records, I.seg_max int4 at a 16-byte boundary]
 //        [queue ring I.lcap].
 // ===================================================================== //
+enum { MODE_ANT = 0, MODE_INIT = 1, MODE_INIT_FIRST = 2, MODE_INIT_MORE = 3 };
 __host__ __device__ inline int seg_lds_words(int tw_words, int W) { return (tw_words + 3 * W + 3) & ~3; }
 
 // The queue and bitmaps the local search starts from (leader wave); returns
 // the flags it runs with.
-FACO_DEV uint32_t search_setup(const Inst &I, bool init, int W, int nchk, int32_t *ring,
+FACO_DEV uint32_t search_setup(const Inst &I, int mode, int W, int nchk, int32_t *ring,
                                uint32_t *vis, uint32_t *inq, uint32_t *ord, Queue &Q,
                                LaneCounters &cnt) {
   const int n = I.n, lane = lane_id();
   uint32_t flags = I.ls_flags;
   const int lcap = I.lcap;
-  if (init) {
+  if (mode == MODE_INIT_MORE) {
+    // the cities the sweep marked, in ascending original number
+    for (int w = lane; w < W; w += kWave) {
+      ord[w] = I.marks[w];
+      inq[w] = 0u;
+      vis[w] = 0u;
+      I.marks[w] = 0u;
+    }
+    Q.in_lds = 1;
+    Q.cap = lcap;
+    Q.head = Q.tail = Q.count = 0;
+    wave_fence();
+    list_marked(I, W, Q, inq, vis, ord);
+    wave_fence();
+    return LS_2OPT | (I.ls_flags & LS_OROPT);
+  }
+  if (mode != MODE_ANT) {
     // the initial solution reports only its local-search counters
 #pragma unroll
     for (int c = 0; c < CNT_LS_POPS; ++c) cnt[c] = 0;
     // with 3-opt, the initial search runs in init_search_kernel afterwards
-    flags = (I.ls_flags & LS_INIT_3OPT) ? 0u : (LS_2OPT | LS_SWEEP | (I.ls_flags & LS_OROPT));
+    flags = LS_2OPT | (mode == MODE_INIT ? LS_SWEEP : 0u) | (I.ls_flags & LS_OROPT);
+    if (I.ls_flags & LS_INIT_3OPT) flags = 0u;
+    if (mode == MODE_INIT_FIRST)
+      for (int w = lane; w < W; w += kWave) I.marks[w] = 0u;
     Q.in_lds = n <= lcap ? 1 : 0;
     Q.cap = Q.in_lds ? lcap : n;
     // every city listed, in ascending original number
@@ -1357,11 +1382,15 @@ FACO_DEV void run_ant(const Inst &I, int ant, int mode, uint32_t *lds) {
   int32_t *ring = I.ring + (size_t)ant * (size_t)n;
   int2 *rxy = I.rxy + (size_t)ant * (size_t)n;
   const int w = TW > 1 ? uniform_i((int)(threadIdx.x >> 6)) : 0;
+  const bool init = mode != MODE_ANT, more = mode == MODE_INIT_MORE;
+  if (more && uniform_i(I.st->init_done)) return;
   LaneCounters cnt, tk;
-  const bool init = mode == 1;
-  const int64_t t0 = w == 0 ? ticks() : 0;
+  // a later launch of the initial search counts the sweep before it
+  const int64_t t0 = w == 0 ? (more ? I.st->init_clock : ticks()) : 0;
   int64_t len = 0;
   uint32_t flags = 0;
+  int changes = more ? uniform_i(I.st->init_changes) : 0, listed = 0;
+  const int changes0 = changes;
   Queue Q;
   Q.lr = SEG ? (int32_t *)(rec + I.seg_max) : (int32_t *)(ord + W);
   Q.gr = ring;
@@ -1371,16 +1400,25 @@ FACO_DEV void run_ant(const Inst &I, int ant, int mode, uint32_t *lds) {
       return;
   } else {
     int nchk = 0;
-    len = init ? construct_greedy<TW>(I, route, pos, rxy, vis, inq, tl, W, cnt)
-               : construct<KT, TW>(I, (uint64_t)I.st->iter + 1, ant, route, pos, rxy, ring, vis,
-                                   inq, tl, W, nchk, cnt, tk);
-    tk[0] = ticks() - t0;
-    flags = search_setup(I, init, W, nchk, ring, vis, inq, ord, Q, cnt);
+    if (more) {
+      len = I.st->init_cur;
+      cnt[CNT_SWEEPS] = 1;
+      tk[TK_SWEEP_CITIES] = n;
+      tk[TK_SWEEP_TESTS] = ticks() - t0;
+    } else {
+      len = init ? construct_greedy<TW>(I, route, pos, rxy, vis, inq, tl, W, cnt)
+                 : construct<KT, TW>(I, (uint64_t)I.st->iter + 1, ant, route, pos, rxy, ring,
+                                     vis, inq, tl, W, nchk, cnt, tk);
+      tk[0] = ticks() - t0;
+    }
+    flags = search_setup(I, mode, W, nchk, ring, vis, inq, ord, Q, cnt);
+    listed = Q.count;
+    if (more) tk[3] = ticks() - t0;
     if constexpr (SEG || TW == 1) {
       if constexpr (SEG) seg_begin(I, ant, rec, tl, TW > 1, SQ);
       if (flags & (LS_2OPT | LS_OROPT))
         len -= local_search<KT, TW, SEG>(I, flags, route, pos, rxy, inq, vis, ord, tl, W, Q, cnt,
-                                         tk, init ? -1 : ant, SQ);
+                                         tk, init ? -1 : ant, SQ, changes);
     }
   }
   if constexpr (TW > 1 && !SEG) {
@@ -1407,7 +1445,7 @@ FACO_DEV void run_ant(const Inst &I, int ant, int mode, uint32_t *lds) {
       Q.in_lds = team_arg(tl, 4);
       flags = (uint32_t)team_arg(tl, 5);
       len -= team_local_search<KT, TW>(I, flags, route, pos, rxy, inq, vis, ord, tl, W, Q, cnt,
-                                       tk, init ? -1 : ant, w);
+                                       tk, init ? -1 : ant, w, changes);
       if (w > 0) return;
     }
   }
@@ -1422,15 +1460,32 @@ FACO_DEV void run_ant(const Inst &I, int ant, int mode, uint32_t *lds) {
     team_sync();
   }
   if (init) {
-    const int32_t *fr = (live ? I.r2 : I.routes) + (size_t)ant * (size_t)n;
-    for (int i = lane; i < n; i += kWave) I.gb_route[i] = fr[i];
-    if (lane == 0) {
-      I.st->gb_len = len;
-      I.st->init_len = len;
+    // whether the search has ended: nothing marked by the sweep, or n moves;
+    // marked cities without a move are the two move tests disagreeing
+    bool done = mode == MODE_INIT || changes >= n;
+    if (more && changes == changes0) {
+      done = true;
+      if (uniform_i(listed) > 0) record_fault(I, FAULT_LS_STALL, -1);
     }
-    if (lane < NCNT) I.st->init_cnt[lane] = cnt.v;
-    tk[4] = ticks() - t0;
-    if (lane < kTicks) I.st->init_ticks[lane] = tk.v;
+    DevState *st = I.st;
+    if (done) {
+      const int32_t *fr = (live ? I.r2 : I.routes) + (size_t)ant * (size_t)n;
+      for (int i = lane; i < n; i += kWave) I.gb_route[i] = fr[i];
+    }
+    const int64_t t1 = ticks();
+    tk[4] = t1 - t0;
+    if (lane == 0) {
+      st->init_done = done ? 1 : 0;
+      st->init_changes = changes;
+      st->init_cur = len;
+      st->init_clock = t1;
+      if (done) {
+        st->gb_len = len;
+        st->init_len = len;
+      }
+    }
+    if (lane < NCNT) st->init_cnt[lane] = cnt.v + (more ? st->init_cnt[lane] : 0);
+    if (lane < kTicks) st->init_ticks[lane] = tk.v + (more ? st->init_ticks[lane] : 0);
   } else {
     if (lane == 0) {
       I.lens[ant] = len;
@@ -1442,6 +1497,23 @@ FACO_DEV void run_ant(const Inst &I, int ant, int mode, uint32_t *lds) {
     }
     tk[4] = ticks() - t0;
     if (lane < kTicks) I.ticks[(size_t)ant * kTicks + lane] += tk.v;
+  }
+}
+
+// One sweep of the initial search over all cities (its tour is ant slot 0's),
+// a city per lane in label order: marks the improvable ones by original
+// number.  The tour does not change meanwhile, so the whole chip shares it: a
+// sweep of 100k cities takes 52 us (launch included) instead of one 8-wave
+// workgroup's 5.7 ms.
+template <int KT>
+__global__ void __launch_bounds__(256) init_sweep_kernel(Inst I) {
+  if (I.st->init_done) return;
+  const int x = (int)(blockIdx.x * blockDim.x + threadIdx.x);
+  if (x >= I.n) return;
+  const uint32_t flags = LS_2OPT | (I.ls_flags & LS_OROPT);
+  if (has_improving<KT>(I, flags, x, I.routes, I.pos, I.rxy)) {
+    const int o = I.orig_of[x];
+    atomicOr(&I.marks[o >> 5], 1u << (o & 31));
   }
 }
 

@@ -332,16 +332,17 @@ FACO_DEV int team_sweep(const Inst &I, uint32_t flags, int W, Queue &Q, const Fl
 
 // The local search (Alg. 3 + Or-opt + sweeps), called by every wave w of the
 // team with the same arguments; cnt, tk and the return value (the gain) are
-// wave 0's.
+// wave 0's.  changes: moves made before (in) and by the end (out).
 template <int KT, int TW>
 FACO_DEV int64_t team_local_search(const Inst &I, uint32_t flags, int32_t *route, int32_t *pos,
                                    int2 *rxy, uint32_t *inq, uint32_t *touched, uint32_t *ord,
                                    TeamLds *tl, int W, Queue Q, LaneCounters &cnt,
-                                   LaneCounters &tk, int ant, int w) {
+                                   LaneCounters &tk, int ant, int w, int &changes) {
   constexpr int GS = KT <= 16 ? 16 : 32;
   const int n = I.n, lane = lane_id();
   flags = (uint32_t)uniform_i((int)flags);
-  int changes = 0, changes_at_sweep = -1, par = 0;
+  const int changes0 = changes;
+  int changes_at_sweep = -1, par = 0;
   int pops = 0, m2 = 0, sweeps = 0, rounds = 0;
   int64_t gain = 0, moved = 0, t_eval = 0, t_apply = 0, t_sweep = 0;
   const TeamLane tlane = team_lane<GS>(I, flags);
@@ -362,13 +363,16 @@ FACO_DEV int64_t team_local_search(const Inst &I, uint32_t flags, int32_t *route
       int *desc = tl->ls.desc[par];
       par ^= 1;
       if (w < gcount) {
-        int h = Q.head + w;
-        h = h >= Q.cap ? h - Q.cap : h;
-        int a = Q.lr[Q.in_lds ? h : 0];
-        if (!Q.in_lds) a = Q.gr[h];
-        a = uniform_i(a);
-        if (uniform_i(pre_a) != a) pre = team_pre<GS>(I, a);
-        pre.a = a;
+        pre_a = uniform_i(pre_a);
+        if (pre_a < 0) {
+          int h = Q.head + w;
+          h = h >= Q.cap ? h - Q.cap : h;
+          int a = Q.lr[Q.in_lds ? h : 0];
+          if (!Q.in_lds) a = Q.gr[h];
+          pre_a = uniform_i(a);
+          pre = team_pre<GS>(I, pre_a);
+        }
+        pre.a = pre_a;
         team_eval<GS>(I, tlane, pre, route, pos, rxy, desc + w * kDescWords);
       }
       team_sync();
@@ -385,12 +389,15 @@ FACO_DEV int64_t team_local_search(const Inst &I, uint32_t flags, int32_t *route
       Q.count -= npop;
       pops += npop;
       ++rounds;
-      // the next round's city of this wave, unless a push comes before it
+      // the next round's city of this wave, if it is listed already (the
+      // move's cities go to the tail)
       pre_a = -1;
-      if (Q.in_lds && w < Q.count) {
+      if (w < Q.count) {
         int h = Q.head + w;
         h = h >= Q.cap ? h - Q.cap : h;
-        pre_a = uniform_i(Q.lr[h]);
+        int a = Q.lr[Q.in_lds ? h : 0];
+        if (!Q.in_lds) a = Q.gr[h];
+        pre_a = uniform_i(a);
         pre = team_pre<GS>(I, pre_a);
       }
       if (w == 0) {
@@ -425,10 +432,13 @@ FACO_DEV int64_t team_local_search(const Inst &I, uint32_t flags, int32_t *route
         const int np = two ? 4 : 6;
         const int x = rec[lane < np ? k : 0];
         bool take = lane < np && !bit_get(inq, lane < np ? x : 0);
+        // the ends of a 2-opt move are four cities; an Or-opt move's may repeat
+        if (!two) {
 #pragma unroll
-        for (int i = 0; i < 5; ++i) {
-          const int xi = readlane_i(x, i);
-          if (i < lane && xi == x) take = false;
+          for (int i = 0; i < 5; ++i) {
+            const int xi = readlane_i(x, i);
+            if (i < lane && xi == x) take = false;
+          }
         }
         const uint64_t pm = ballot(take);
         const int cntp = __builtin_popcountll(pm);
@@ -522,7 +532,7 @@ FACO_DEV int64_t team_local_search(const Inst &I, uint32_t flags, int32_t *route
   if (w == 0) {
     cnt[CNT_LS_POPS] += pops;
     cnt[CNT_MOVES_2OPT] += m2;
-    cnt[CNT_MOVES_OROPT] += changes - m2;
+    cnt[CNT_MOVES_OROPT] += changes - changes0 - m2;
     cnt[CNT_MOVED_ELEMS] += moved;
     cnt[CNT_SWEEPS] += sweeps;
     cnt[CNT_LS_GAIN] += gain;
