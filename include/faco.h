@@ -178,9 +178,8 @@ typedef struct faco_batch_config {
                                  captured as a HIP graph and replayed.
                                  Instances with verification on run per
                                  phase.                                     */
-  int32_t team_waves;         /* waves per ant: 0 = by size (as for a lone
-                                 instance, counting the batch's longest tour
-                                 and all its ants), else 1, 4 or 8          */
+  int32_t team_waves;         /* waves per ant: 0 = by the number of ants
+                                 (faco_set_team_waves), else 1, 4 or 8      */
   int32_t ants_per_block;     /* one-wave ants per workgroup: 1, 2 or 4,
                                  lowered when their LDS would not fit a CU  */
   int32_t queue_lds_capacity; /* LDS part of each ant's work queue: 0 = as
@@ -227,12 +226,13 @@ int faco_set_batch_ants_per_block(int32_t ants_per_block);
 
 /* Waves per ant in the ant kernels, for instances built after the call and
  * for faco_run_batch launches after it (process-wide): 1, 4 or 8, or 0 for a
- * choice by size (1 below 2048 cities; else 8 up to 256 ants, 4 up to 512,
- * 1 beyond; a batch counts its largest tour and all its ants).  Wave 0 of an
- * ant makes every decision; the others share its wide steps (speculative
- * source-following windows of 64 steps per wave, the array rewrites of 2-opt
- * and Or-opt moves, sweep tests).  An execution-shape choice that never
- * changes results.  Errors: FACO_EINVAL. */
+ * choice by the number of ants (8 up to 256, 4 up to 2048, 1 beyond; a batch
+ * counts all its ants, and takes 4 beyond 2048 too while its tours' mean
+ * length is below half the longest).  Wave 0 of an ant makes every decision of
+ * the construction and the others share its wide steps (speculative
+ * source-following windows, copies, nearest-city scans); the local search is
+ * run by all waves (a listed city each, the array rewrites, sweep tests).  An
+ * execution-shape choice that never changes results.  Errors: FACO_EINVAL. */
 int faco_set_team_waves(int32_t team_waves);
 
 /* Capacity (entries) of the LDS part of each ant's work queue of listed

@@ -585,15 +585,20 @@ FACO_DEV bool has_improving(const Inst &I, uint32_t flags, int x, const FlatT &T
 
 #include "faco_seg.hpp"
 
-constexpr int kChunks = 16;  // 64-element chunks in flight per wave and round
-// Chunks in flight per wave of a team rewrite (one round covers
-// TW * kTeamChunks * 64 pairs).
-constexpr int kTeamChunks = 16;
+// 64-element chunks in flight per wave and round of a rewrite.  More hide more
+// of a long rewrite's latency and take eight registers each: 8-wave teams (one
+// ant per CU, long tours) hold 16, which keeps 2 waves per SIMD; 4-wave teams
+// 8 and lone waves 4, so that the many ants of a batch run beside each other
+// (4 waves per SIMD with 4-wave teams).  A batch of 64 instances of 200..5000
+// cities takes 0.71 ms an iteration on 4-wave teams with 8 chunks and 0.83 with
+// 16; a 100k run 4.25 ms on 8-wave teams with 16 and 4.28 with 8.
+template <int TW>
+constexpr int team_chunks() { return TW == 8 ? 16 : (TW == 4 ? 8 : 4); }
 
 // Reverse the cyclic array range of length L starting at s: pairs (i,
 // L-1-i) are disjoint, so the 64-pair chunks are dealt to the waves of a
 // team of TW in turn (chunk c to wave c mod TW), CH per wave in flight.
-template <int TW, int CH = kChunks>
+template <int TW, int CH = team_chunks<TW>()>
 FACO_DEV void reverse_part(int n, int s, int L, int w, int32_t *route, int32_t *pos,
                            int2 *rxy) {
   const int lane = lane_id();
@@ -635,7 +640,7 @@ FACO_DEV void reverse_part(int n, int s, int L, int w, int32_t *route, int32_t *
 // rounds descend.  A round reads TW * CH * 64 elements, then (after a
 // barrier when TW > 1) writes them: no round reads what a later-starting
 // write of another wave could clobber.
-template <int TW, int CH = kChunks>
+template <int TW, int CH = team_chunks<TW>()>
 FACO_DEV void shift_part(int n, int src, int dst, int D, bool down, int w, int32_t *route,
                          int32_t *pos, int2 *rxy) {
   const int lane = lane_id();
@@ -1519,7 +1524,7 @@ __global__ void __launch_bounds__(256) init_sweep_kernel(Inst I) {
 
 // One workgroup of TW waves per ant.
 template <int KT, int TW, bool SEG = false>
-__global__ void __launch_bounds__(64 * TW) ant_kernel(Inst I, int mode) {
+__global__ void __launch_bounds__(64 * TW, TW == 4 && !SEG ? 4 : 1) ant_kernel(Inst I, int mode) {
   extern __shared__ uint32_t lds[];
   run_ant<KT, TW, SEG>(I, (int)blockIdx.x, mode, lds);
 }
@@ -1533,7 +1538,7 @@ __global__ void __launch_bounds__(64 * TW) ant_kernel(Inst I, int mode) {
 //          (TW > 1: of block w, whose TW waves form the ant's team)
 // ===================================================================== //
 template <int KT, int TW>
-__global__ void __launch_bounds__(TW > 1 ? 64 * TW : 256)
+__global__ void __launch_bounds__(TW > 1 ? 64 * TW : 256, TW == 4 ? 4 : 1)
     ant_batch_kernel(const Inst *insts, const int2 *amap, int total, int apb, int lds_words) {
   extern __shared__ uint32_t lds[];
   if (TW > 1) {

@@ -214,7 +214,7 @@ FACO_DEV void team_reverse_share(int n, int s, int L, int w, int32_t *route, int
   else if (half <= 4 * TW * kWave)
     reverse_part<TW, 4>(n, s, L, ww, route, pos, rxy);
   else
-    reverse_part<TW, kTeamChunks>(n, s, L, ww, route, pos, rxy);
+    reverse_part<TW>(n, s, L, ww, route, pos, rxy);
 }
 
 // A block move by the team, or by wave 1 alone while it holds the whole block
@@ -233,7 +233,7 @@ FACO_DEV void team_shift_share(int n, int src, int dst, int D, bool down, int w,
   else if (D <= 4 * TW * kWave)
     shift_part<TW, 4>(n, src, dst, D, down, ww, route, pos, rxy);
   else
-    shift_part<TW, kTeamChunks>(n, src, dst, D, down, ww, route, pos, rxy);
+    shift_part<TW>(n, src, dst, D, down, ww, route, pos, rxy);
 }
 
 // Sweep by all waves (see sweep()): the touched cities are gathered into a
