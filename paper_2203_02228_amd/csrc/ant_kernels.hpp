@@ -21,6 +21,10 @@ AntPersistFn faco_ant_persist_kernel(int k, int tw);
 // one sweep of the initial search over all cities
 typedef void (*InitSweepFn)(faco::Inst);
 InitSweepFn faco_init_sweep_kernel(int k);
+// the same for the initial search with 3-opt, and that search (8 waves; mode
+// MODE_INIT_FIRST or MODE_INIT_MORE)
+InitSweepFn faco_init_sweep3_kernel(int k);
+AntKernelFn faco_init_search_kernel(int k);
 // LDS words of the team area ahead of an ant's bitmaps
 int faco_team_lds_words(int tw);
 // ant kernel whose local search runs on segment-list tours (Inst.seg_on)

@@ -18,7 +18,6 @@
 #include "../../include/faco.h"
 #include "ant_kernels.hpp"
 #include "faco_aux.hpp"
-#include "faco_init.hpp"
 
 using faco::DevState;
 using faco::Inst;
@@ -647,31 +646,40 @@ extern "C" int faco_build_instance(const int32_t *xy, int32_t n, const faco_para
   auto launch_init = [&](int mode) {
     hipLaunchKernelGGL(initk, dim3(1), dim3(64 * h->tw), h->lds_init, h->stream, I, mode);
   };
-  if (n < kChipSweepMin || (p->ls_flags & FACO_LS_INIT_3OPT)) {
+  // the search in a launch per sweep; its end is looked for every few sweeps
+  // (launches after it return at once).  Every launch before the end makes at
+  // least one of at most n moves.
+  auto search_chain = [&](AntKernelFn searchk, int waves, size_t lds, InitSweepFn sweepk,
+                          int cities_per_block) -> hipError_t {
+    const dim3 grid((unsigned)((n + cities_per_block - 1) / cities_per_block));
+    do {
+      for (int r = 0; r < 3; ++r) {
+        hipLaunchKernelGGL(sweepk, grid, dim3(256), 0, h->stream, I);
+        hipLaunchKernelGGL(searchk, dim3(1), dim3(64 * waves), lds, h->stream, I, 3);
+      }
+      hipError_t ce = hipGetLastError();
+      if (ce == hipSuccess)
+        ce = hipMemcpyAsync(&hs, I.st, sizeof(DevState), hipMemcpyDeviceToHost, h->stream);
+      if (ce == hipSuccess) ce = hipStreamSynchronize(h->stream);
+      if (ce != hipSuccess) return ce;
+    } while (!hs.init_done);
+    return hipSuccess;
+  };
+  if (p->ls_flags & FACO_LS_INIT_3OPT) {
+    // the nearest-neighbour tour, then the search with 3-opt
+    launch_init(1);
+    const AntKernelFn searchk = faco_init_search_kernel(h->k);
+    const size_t lds = sizeof(uint32_t) * ((size_t)faco_team_lds_words(8) + 3 * ((N + 31) / 32) +
+                                           (size_t)I.lcap);
+    BTRY(hipFuncSetAttribute((const void *)searchk, hipFuncAttributeMaxDynamicSharedMemorySize,
+                             (int)lds));
+    hipLaunchKernelGGL(searchk, dim3(1), dim3(64 * 8), lds, h->stream, I, 2);
+    BTRY(search_chain(searchk, 8, lds, faco_init_sweep3_kernel(h->k), 4));
+  } else if (n < kChipSweepMin) {
     launch_init(1);
   } else {
-    // a launch per sweep; the search's end is looked for every few sweeps
-    // (launches after it return at once).  Every launch before the end makes
-    // at least one of at most n moves.
     launch_init(2);
-    for (;;) {
-      for (int r = 0; r < 3; ++r) {
-        hipLaunchKernelGGL(faco_init_sweep_kernel(h->k), dim3((unsigned)((n + 255) / 256)),
-                           dim3(256), 0, h->stream, I);
-        launch_init(3);
-      }
-      BTRY(hipGetLastError());
-      BTRY(hipMemcpyAsync(&hs, I.st, sizeof(DevState), hipMemcpyDeviceToHost, h->stream));
-      BTRY(hipStreamSynchronize(h->stream));
-      if (hs.init_done) break;
-    }
-  }
-  if (p->ls_flags & FACO_LS_INIT_3OPT) {
-    // the initial search with 3-opt, on the nearest-neighbour tour
-    const size_t ilds = sizeof(uint32_t) * 2 * ((N + 31) / 32);
-    BTRY(hipFuncSetAttribute((const void *)faco::init_search_kernel,
-                             hipFuncAttributeMaxDynamicSharedMemorySize, (int)ilds));
-    hipLaunchKernelGGL(faco::init_search_kernel, dim3(1), dim3(64), ilds, h->stream, I);
+    BTRY(search_chain(initk, h->tw, h->lds_init, faco_init_sweep_kernel(h->k), 256));
   }
   hipLaunchKernelGGL(faco::init_state_kernel, dim3(1), dim3(1), 0, h->stream, I);
   hipLaunchKernelGGL(faco::source_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0,

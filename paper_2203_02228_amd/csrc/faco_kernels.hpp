@@ -1373,6 +1373,38 @@ FACO_DEV uint32_t search_setup(const Inst &I, int mode, int W, int nchk, int32_t
   return flags;
 }
 
+// End of a launch of the initial search (wave 0): its state, counters and ticks
+// (added to the earlier launches' with add_cnt, add_tk), and the global best
+// once the search has ended: in MODE_INIT, when the sweep marked nothing, or at
+// n moves.  Marked cities without a move are the two move tests disagreeing.
+FACO_DEV void init_finish(const Inst &I, int mode, const int32_t *route, int64_t len, int changes,
+                          int changes0, int listed, bool add_cnt, bool add_tk, int64_t t0,
+                          LaneCounters &cnt, LaneCounters &tk) {
+  const int n = I.n, lane = lane_id();
+  DevState *st = I.st;
+  bool done = mode == MODE_INIT || changes >= n;
+  if (mode == MODE_INIT_MORE && changes == changes0) {
+    done = true;
+    if (uniform_i(listed) > 0) record_fault(I, FAULT_LS_STALL, -1);
+  }
+  if (done)
+    for (int i = lane; i < n; i += kWave) I.gb_route[i] = route[i];
+  const int64_t t1 = ticks();
+  tk[4] = t1 - t0;
+  if (lane == 0) {
+    st->init_done = done ? 1 : 0;
+    st->init_changes = changes;
+    st->init_cur = len;
+    st->init_clock = t1;
+    if (done) {
+      st->gb_len = len;
+      st->init_len = len;
+    }
+  }
+  if (lane < NCNT) st->init_cnt[lane] = cnt.v + (add_cnt ? st->init_cnt[lane] : 0);
+  if (lane < kTicks) st->init_ticks[lane] = tk.v + (add_tk ? st->init_ticks[lane] : 0);
+}
+
 template <int KT, int TW, bool SEG = false>
 FACO_DEV void run_ant(const Inst &I, int ant, int mode, uint32_t *lds) {
   const int n = I.n, lane = lane_id();
@@ -1430,24 +1462,16 @@ FACO_DEV void run_ant(const Inst &I, int ant, int mode, uint32_t *lds) {
     // the whole team runs the local search
     if (w == 0) {
       const bool search = (flags & (LS_2OPT | LS_OROPT)) != 0;
+      queue_share(tl, Q);
       if (lane == 0) {
         tl->op = search ? OP_SEARCH : OP_EXIT;
-        tl->arg[0] = Q.head;
-        tl->arg[1] = Q.tail;
-        tl->arg[2] = Q.count;
-        tl->arg[3] = Q.cap;
-        tl->arg[4] = Q.in_lds;
         tl->arg[5] = (int)flags;
       }
       team_sync();
       if (!search) flags = 0;
     }
     if (w > 0 || flags) {
-      Q.head = team_arg(tl, 0);
-      Q.tail = team_arg(tl, 1);
-      Q.count = team_arg(tl, 2);
-      Q.cap = team_arg(tl, 3);
-      Q.in_lds = team_arg(tl, 4);
+      queue_take(tl, Q);
       flags = (uint32_t)team_arg(tl, 5);
       len -= team_local_search<KT, TW>(I, flags, route, pos, rxy, inq, vis, ord, tl, W, Q, cnt,
                                        tk, init ? -1 : ant, w, changes);
@@ -1465,32 +1489,8 @@ FACO_DEV void run_ant(const Inst &I, int ant, int mode, uint32_t *lds) {
     team_sync();
   }
   if (init) {
-    // whether the search has ended: nothing marked by the sweep, or n moves;
-    // marked cities without a move are the two move tests disagreeing
-    bool done = mode == MODE_INIT || changes >= n;
-    if (more && changes == changes0) {
-      done = true;
-      if (uniform_i(listed) > 0) record_fault(I, FAULT_LS_STALL, -1);
-    }
-    DevState *st = I.st;
-    if (done) {
-      const int32_t *fr = (live ? I.r2 : I.routes) + (size_t)ant * (size_t)n;
-      for (int i = lane; i < n; i += kWave) I.gb_route[i] = fr[i];
-    }
-    const int64_t t1 = ticks();
-    tk[4] = t1 - t0;
-    if (lane == 0) {
-      st->init_done = done ? 1 : 0;
-      st->init_changes = changes;
-      st->init_cur = len;
-      st->init_clock = t1;
-      if (done) {
-        st->gb_len = len;
-        st->init_len = len;
-      }
-    }
-    if (lane < NCNT) st->init_cnt[lane] = cnt.v + (more ? st->init_cnt[lane] : 0);
-    if (lane < kTicks) st->init_ticks[lane] = tk.v + (more ? st->init_ticks[lane] : 0);
+    const int32_t *fr = (live ? I.r2 : I.routes) + (size_t)ant * (size_t)n;
+    init_finish(I, mode, fr, len, changes, changes0, listed, more, more, t0, cnt, tk);
   } else {
     if (lane == 0) {
       I.lens[ant] = len;

@@ -98,8 +98,9 @@ FACO_DEV TeamLane team_lane(const Inst &I, uint32_t flags) {
 // Evaluate city a with the whole wave.  The result is the best move in the
 // order of the sequential evaluation: 2-opt first (loop 1 over the list, then
 // loop 2), else Or-opt by gain, then slot, list position, succ before pred.
+// Leaves the move in desc and returns its gain (0: none; uniform).
 template <int GS>
-FACO_DEV void team_eval(const Inst &I, const TeamLane &T, const TeamPre &P,
+FACO_DEV int team_eval(const Inst &I, const TeamLane &T, const TeamPre &P,
                         const int32_t *route, const int32_t *pos, const int2 *rxy, int *desc) {
   const int n = I.n;
   // opaque: masks of lanes are compared afresh instead of kept (and spilled)
@@ -200,6 +201,96 @@ FACO_DEV void team_eval(const Inst &I, const TeamLane &T, const TeamPre &P,
     d4[1] = make_int4(pb, pbn, pa, a);
   }
   if (lane < 7) d4[2 + lane] = make_int4(nb, U.x, U.y, 0);
+  return best;
+}
+
+// The 3-opt trial of the initial search, by the whole wave, for a city a
+// without 2-opt or Or-opt move: remove (t1, t2), (t3, t4), (t5, t6), add (t2,
+// t3), (t4, t5), (t6, t1), with t1 = a, t2 its neighbour in direction dir, t3 =
+// slot s of t2's list, t5 = slot r of t4's list, all positive partial gains, t5
+// on the path t2 .. t3 before t3.  Variant (dir K + s) K + r; best gain, first
+// variant.  Lane: a pair (dir, s) and every second r, eight r at a time, so
+// the four levels of dependent loads are taken by all variants together (a
+// loop over single variants per lane took them eight times over).
+// Record: [0] gain, code kThreeOpt + dir   [1] position of t2, offsets of t3
+// and t5 from it, a   [2 + j] t_(j+1).  Returns the gain (0: none; uniform).
+constexpr int kThreeOpt = 32;
+FACO_DEV int team_eval3(const Inst &I, int a, const int32_t *route, const int32_t *pos,
+                        const int2 *rxy, int *desc) {
+  constexpr int RB = 8;
+  const int n = I.n, K = I.k, lane = lane_id();
+  const int pa = uniform_i(at(pos, a));
+  const int2 xa = at(rxy, pa);
+  int best = 0, bc = 0, bdir = 0, bp2 = 0, bo3 = 0, bo5 = 0;
+  int b2 = 0, b3 = 0, b4 = 0, b5 = 0, b6 = 0;
+  for (int q0 = 0; q0 < 2 * K; q0 += kWave / 2) {
+    const int q = q0 + (lane >> 1), qc = q < 2 * K ? q : 0;
+    const int dir = qc >= K ? 1 : 0, s = qc - dir * K, fwd = dir ? -1 : 1;
+    const int p2 = wrapc(pa + fwd, n);
+    const int t2 = at(route, p2);
+    const int t3 = at(I.cl, t2 * K + s);
+    int g1 = cost(xa, at(rxy, p2)) - at(I.cl_d, t2 * K + s);
+    const int p3 = at(pos, t3), p4 = wrapc(p3 + fwd, n);
+    const int t4 = at(route, p4);
+    const bool ok = q < 2 * K && g1 > 0 && t3 != a && t4 != a;
+    g1 += cost(at(rxy, p3), at(rxy, p4));
+    const int off3 = wrapc(dir ? p2 - p3 : p3 - p2, n);
+    for (int r0 = 0; r0 < K; r0 += 2 * RB) {
+      int t5[RB], g2[RB];
+#pragma unroll
+      for (int i = 0; i < RB; ++i) {
+        const int r = r0 + 2 * i + (lane & 1);
+        const bool in = ok && r < K;
+        t5[i] = in ? at(I.cl, t4 * K + r) : a;
+        g2[i] = in ? g1 - at(I.cl_d, t4 * K + r) : 0;
+      }
+      int p5[RB];
+#pragma unroll
+      for (int i = 0; i < RB; ++i) p5[i] = at(pos, t5[i]);
+      int t6[RB];
+      int2 x5[RB], x6[RB];
+#pragma unroll
+      for (int i = 0; i < RB; ++i) {
+        const int p6 = wrapc(p5[i] + fwd, n);
+        t6[i] = at(route, p6);
+        x5[i] = at(rxy, p5[i]);
+        x6[i] = at(rxy, p6);
+      }
+#pragma unroll
+      for (int i = 0; i < RB; ++i) {
+        const int off5 = wrapc(dir ? p2 - p5[i] : p5[i] - p2, n);
+        const int g = g2[i] + cost(x5[i], x6[i]) - cost(x6[i], xa);
+        if (g2[i] > 0 && off5 < off3 && g > best) {
+          best = g;
+          bc = q * K + r0 + 2 * i + (lane & 1);
+          bdir = dir;
+          bp2 = p2;
+          bo3 = off3;
+          bo5 = off5;
+          b2 = t2;
+          b3 = t3;
+          b4 = t4;
+          b5 = t5[i];
+          b6 = t6[i];
+        }
+      }
+    }
+  }
+  const int top = wave_max_i32(best);
+  if (top == 0) return 0;
+  const int first = wave_min_i32(best == top ? bc : 0x7fffffff);
+  if (best == top && bc == first) {
+    int4 *d4 = reinterpret_cast<int4 *>(desc);
+    d4[0] = make_int4(top, kThreeOpt + bdir, 0, 0);
+    d4[1] = make_int4(bp2, bo3, bo5, a);
+    d4[2].x = a;
+    d4[3].x = b2;
+    d4[4].x = b3;
+    d4[5].x = b4;
+    d4[6].x = b5;
+    d4[7].x = b6;
+  }
+  return top;
 }
 
 // This wave's share of a reversal (see reverse_part): few chunks take the
@@ -234,6 +325,24 @@ FACO_DEV void team_shift_share(int n, int src, int dst, int D, bool down, int w,
     shift_part<TW, 4>(n, src, dst, D, down, ww, route, pos, rxy);
   else
     shift_part<TW>(n, src, dst, D, down, ww, route, pos, rxy);
+}
+
+// The queue's state from wave 0 to the other waves (a barrier between).
+FACO_DEV void queue_share(TeamLds *tl, const Queue &Q) {
+  if (lane_id() == 0) {
+    tl->arg[0] = Q.head;
+    tl->arg[1] = Q.tail;
+    tl->arg[2] = Q.count;
+    tl->arg[3] = Q.cap;
+    tl->arg[4] = Q.in_lds;
+  }
+}
+FACO_DEV void queue_take(const TeamLds *tl, Queue &Q) {
+  Q.head = team_arg(tl, 0);
+  Q.tail = team_arg(tl, 1);
+  Q.count = team_arg(tl, 2);
+  Q.cap = team_arg(tl, 3);
+  Q.in_lds = team_arg(tl, 4);
 }
 
 // Sweep by all waves (see sweep()): the touched cities are gathered into a
@@ -311,29 +420,20 @@ FACO_DEV int team_sweep(const Inst &I, uint32_t flags, int W, Queue &Q, const Fl
     if (w == 0) {
       const int64_t tl0 = ticks();
       list_marked(I, W, Q, inq, touched, ord);
-      if (lane == 0) {
-        tl->arg[0] = Q.head;
-        tl->arg[1] = Q.tail;
-        tl->arg[2] = Q.count;
-        tl->arg[3] = Q.cap;
-        tl->arg[4] = Q.in_lds;
-      }
+      queue_share(tl, Q);
       tk[TK_SWEEP_LIST] += ticks() - tl0;
     }
     team_sync();
-    Q.head = team_arg(tl, 0);
-    Q.tail = team_arg(tl, 1);
-    Q.count = team_arg(tl, 2);
-    Q.cap = team_arg(tl, 3);
-    Q.in_lds = team_arg(tl, 4);
+    queue_take(tl, Q);
   }
   return listed;
 }
 
 // The local search (Alg. 3 + Or-opt + sweeps), called by every wave w of the
 // team with the same arguments; cnt, tk and the return value (the gain) are
-// wave 0's.  changes: moves made before (in) and by the end (out).
-template <int KT, int TW>
+// wave 0's.  changes: moves made before (in) and by the end (out).  OPT3: the
+// initial search with 3-opt (no sweeps of its own).
+template <int KT, int TW, bool OPT3 = false>
 FACO_DEV int64_t team_local_search(const Inst &I, uint32_t flags, int32_t *route, int32_t *pos,
                                    int2 *rxy, uint32_t *inq, uint32_t *touched, uint32_t *ord,
                                    TeamLds *tl, int W, Queue Q, LaneCounters &cnt,
@@ -343,7 +443,7 @@ FACO_DEV int64_t team_local_search(const Inst &I, uint32_t flags, int32_t *route
   flags = (uint32_t)uniform_i((int)flags);
   const int changes0 = changes;
   int changes_at_sweep = -1, par = 0;
-  int pops = 0, m2 = 0, sweeps = 0, rounds = 0;
+  int pops = 0, m2 = 0, m3 = 0, sweeps = 0, rounds = 0;
   int64_t gain = 0, moved = 0, t_eval = 0, t_apply = 0, t_sweep = 0;
   const TeamLane tlane = team_lane<GS>(I, flags);
   TeamPre pre;
@@ -373,7 +473,8 @@ FACO_DEV int64_t team_local_search(const Inst &I, uint32_t flags, int32_t *route
           pre = team_pre<GS>(I, pre_a);
         }
         pre.a = pre_a;
-        team_eval<GS>(I, tlane, pre, route, pos, rxy, desc + w * kDescWords);
+        const int found = team_eval<GS>(I, tlane, pre, route, pos, rxy, desc + w * kDescWords);
+        if (OPT3 && found == 0) team_eval3(I, pre.a, route, pos, rxy, desc + w * kDescWords);
       }
       team_sync();
       // lanes 2 v and 2 v + 1 hold the head of wave v's record
@@ -412,7 +513,7 @@ FACO_DEV int64_t team_local_search(const Inst &I, uint32_t flags, int32_t *route
       const int pb = readlane_i(v.x, jb + 1), pbn = readlane_i(v.y, jb + 1);
       const int pa = readlane_i(v.z, jb + 1);
       const int *rec = desc + j * kDescWords;
-      const bool two = code < 2;
+      const bool two = code < 2, three = OPT3 && code >= kThreeOpt;
       const int side = code & 1, slot = (code - 2) >> 1;
       int dir, L, lf, ll, lp, lq;
       or_slot_lanes(slot, dir, L, lf, ll, lp, lq);
@@ -426,8 +527,10 @@ FACO_DEV int64_t team_local_search(const Inst &I, uint32_t flags, int32_t *route
                         : (lane == 1 ? (side ? 8 + 4 * 3 : 8 + 4 * 4)
                                      : ((lane == 2) == (side == 0) ? 2 : 3));
         } else {
-          const int jn = lane == 0 ? lp : (lane == 1 ? lq : (lane == 4 ? lf : ll));
-          k = lane == 2 || lane == 3 ? lane : 8 + 4 * jn;
+          // 3-opt: t1 .. t6
+          const int jn = three ? lane
+                               : (lane == 0 ? lp : (lane == 1 ? lq : (lane == 4 ? lf : ll)));
+          k = !three && (lane == 2 || lane == 3) ? lane : 8 + 4 * jn;
         }
         const int np = two ? 4 : 6;
         const int x = rec[lane < np ? k : 0];
@@ -464,6 +567,18 @@ FACO_DEV int64_t team_local_search(const Inst &I, uint32_t flags, int32_t *route
         mv = first ? L1 : n - L1;
         team_reverse_share<TW>(n, uniform_i(first ? px : pz), uniform_i(mv), w, route, pos, rxy);
         ++m2;
+      } else if (three) {
+        // the blocks t2 .. t5 and t6 .. t3 (in direction dir) exchange places:
+        // the whole range reversed, then each block
+        const int p2 = pb, off3 = pbn, off5 = pa;
+        const int s0 = side ? wrapc(p2 - off3, n) : p2;
+        const int L1 = side ? off3 - off5 : off5 + 1, L2 = side ? off5 + 1 : off3 - off5;
+        mv = L1 + L2;
+        team_reverse_share<TW>(n, uniform_i(s0), uniform_i(mv), w, route, pos, rxy);
+        team_sync();
+        team_reverse_share<TW>(n, uniform_i(s0), uniform_i(L2), w, route, pos, rxy);
+        team_reverse_share<TW>(n, uniform_i(wrapc(s0 + L2, n)), uniform_i(L1), w, route, pos, rxy);
+        ++m3;
       } else {
         // the segment and the shorter block between its old place and the
         // insertion edge (x1, x2) exchange places
@@ -509,7 +624,7 @@ FACO_DEV int64_t team_local_search(const Inst &I, uint32_t flags, int32_t *route
       Q.count += np;
     }
     changes = uniform_i(changes);
-    if (!(flags & LS_SWEEP) || changes >= n) break;
+    if (OPT3 || !(flags & LS_SWEEP) || changes >= n) break;
     // Every city a sweep lists has an improving move, so a sweep that was
     // followed by no change can only come from the two move tests
     // disagreeing: stop instead of spinning, and report it.
@@ -532,7 +647,8 @@ FACO_DEV int64_t team_local_search(const Inst &I, uint32_t flags, int32_t *route
   if (w == 0) {
     cnt[CNT_LS_POPS] += pops;
     cnt[CNT_MOVES_2OPT] += m2;
-    cnt[CNT_MOVES_OROPT] += changes - changes0 - m2;
+    cnt[CNT_MOVES_OROPT] += changes - changes0 - m2 - m3;
+    if (OPT3) cnt[CNT_MOVES_3OPT] += m3;
     cnt[CNT_MOVED_ELEMS] += moved;
     cnt[CNT_SWEEPS] += sweeps;
     cnt[CNT_LS_GAIN] += gain;
