@@ -368,9 +368,10 @@ int faco_set_verify(faco_instance *h, int32_t enable);
  * the events of that many iterations at once, so that none is created while
  * the timed iterations are enqueued; events are reused after
  * faco_phase_times).  faco_phase_times syncs and
- * returns, per phase (0 = ants: construction + local search, 1 = colony
- * update, 2 = source materialisation, 3 = pheromone update), the summed
- * milliseconds in ms_out[phase] and the launch count in launches[phase]. */
+ * returns, per phase (0 = ants: construction + local search, 3 = the update:
+ * colony, source materialisation and pheromone in one launch; 1 and 2, once
+ * launches of their own, stay 0), the summed milliseconds in ms_out[phase] and
+ * the launch count in launches[phase]. */
 int faco_set_timing(faco_instance *h, int32_t enable);
 int faco_phase_times(faco_instance *h, double *ms_out /* [4] */,
                      int64_t *launches /* [4] */);

@@ -345,7 +345,7 @@ extern "C" uint64_t faco_footprint_bytes(int32_t n, const faco_params *p) {
   b += 4 * align_up(4 * N * (uint64_t)k);   // cl, cost, eta, tau
   b += 2 * align_up(4 * NB * (((uint64_t)k + 3) & ~(uint64_t)3));  // source-ordered weight, position
   b += align_up(4 * N * (uint64_t)bl + 4); // backup lists
-  b += 4 * align_up(4 * N) + 2 * align_up(8 * N); // source route/pos/edge costs/coordinates, adjacency, global best
+  b += 5 * align_up(4 * N) + 2 * align_up(8 * N); // source route/pos/edge costs/coordinates, adjacency, global best and its inverse
   b += 2 * align_up(4 * N);                   // label maps
   b += 3 * align_up(4 * N * A) + align_up(8 * N * A);  // ant routes, pos, rings, tour coordinates
   b += align_up(8 * A) + 2 * align_up(8 * A * faco::NCNT) + align_up(8 * faco::kTicks * A);
@@ -368,33 +368,18 @@ static void enqueue_verify(faco_instance *h, int ants, int iter_ahead) {
                      h->stream, I, ants, iter_ahead);
 }
 
-// enqueue the four phases of one iteration
+// enqueue the two phases of one iteration (ants, update)
 static int enqueue_iteration(faco_instance *h) {
   const Inst &I = h->dv;
-  const int n = h->n;
-  const unsigned nb_src = (unsigned)((n + 255) / 256);
-  const size_t slots = (size_t)n * (size_t)I.ks;
-  const unsigned nb_tau = (unsigned)((slots + 255) / 256);
   TimedLaunch tl;
   if (h->timing) begin_timed(h, 0, tl);
   hipLaunchKernelGGL(I.seg_on ? faco_ant_seg_kernel(h->k, h->tw) : faco_ant_kernel(h->k, h->tw),
                      dim3(h->p.n_ants), dim3(64 * h->tw), h->lds_ant, h->stream, I, 0);
-  if (h->timing) {
-    end_timed(h, tl);
-    begin_timed(h, 1, tl);
-  }
+  if (h->timing) end_timed(h, tl);
   if (I.verify) enqueue_verify(h, 1, 1);
-  hipLaunchKernelGGL(faco::colony_kernel, dim3(1), dim3(64), 0, h->stream, I);
-  if (h->timing) {
-    end_timed(h, tl);
-    begin_timed(h, 2, tl);
-  }
-  hipLaunchKernelGGL(faco::source_kernel, dim3(nb_src), dim3(256), 0, h->stream, I, 0);
-  if (h->timing) {
-    end_timed(h, tl);
-    begin_timed(h, 3, tl);
-  }
-  hipLaunchKernelGGL(faco::pheromone_kernel, dim3(nb_tau), dim3(256), 0, h->stream, I, 0);
+  if (h->timing) begin_timed(h, 3, tl);
+  hipLaunchKernelGGL(faco::update_kernel, dim3(faco::update_blocks(I.n, I.ks)),
+                     dim3(faco::kUpdateBlock), 0, h->stream, I);
   if (h->timing) end_timed(h, tl);
   HIP_TRY(h, hipGetLastError());
   return FACO_OK;
@@ -526,6 +511,7 @@ extern "C" int faco_build_instance(const int32_t *xy, int32_t n, const faco_para
   ALLOC(src_route, int32_t, N);
   ALLOC(src_pos, int32_t, N);
   ALLOC(gb_route, int32_t, N);
+  ALLOC(gb_pos, int32_t, N);
   ALLOC(src_adj, int2, N);
   ALLOC(src_d, int32_t, N);
   ALLOC(src_xy, int2, N);
@@ -682,11 +668,11 @@ extern "C" int faco_build_instance(const int32_t *xy, int32_t n, const faco_para
     BTRY(search_chain(initk, h->tw, h->lds_init, faco_init_sweep_kernel(h->k), 256));
   }
   hipLaunchKernelGGL(faco::init_state_kernel, dim3(1), dim3(1), 0, h->stream, I);
-  hipLaunchKernelGGL(faco::source_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0,
-                     h->stream, I, 1);
+  hipLaunchKernelGGL(faco::init_source_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0,
+                     h->stream, I);
   const size_t slots = N * KS;
-  hipLaunchKernelGGL(faco::pheromone_kernel, dim3((unsigned)((slots + 255) / 256)), dim3(256),
-                     0, h->stream, I, 1);
+  hipLaunchKernelGGL(faco::init_pheromone_kernel, dim3((unsigned)((slots + 255) / 256)),
+                     dim3(256), 0, h->stream, I);
   BTRY(hipGetLastError());
   BTRY(hipStreamSynchronize(h->stream));
 #undef BTRY
@@ -1038,7 +1024,8 @@ static int batch_ant_count(faco_instance *const *hs, int32_t count) {
 struct BatchShape {
   int count = 0, total = 0, kmax = 2, maxn = 0, max_ants = 0, tw = 1, apb = 1;
   bool any_verify = false, persistent = false;
-  size_t lds_words = 0, max_slots = 0, lds_bytes = 0;
+  size_t lds_words = 0, lds_bytes = 0;
+  unsigned max_update = 0;
   AntBatchFn antk = nullptr;
   AntPersistFn persk = nullptr;
 };
@@ -1077,8 +1064,8 @@ static void batch_shape(faco_instance *const *hs, int32_t count, Inst *insts, in
     }
     const size_t words = 3 * (size_t)((h->n + 31) / 32) + (size_t)insts[i].lcap;
     B.lds_words = words > B.lds_words ? words : B.lds_words;
-    const size_t slots = (size_t)h->n * (size_t)h->dv.ks;
-    B.max_slots = slots > B.max_slots ? slots : B.max_slots;
+    const unsigned ub = faco::update_blocks(h->n, h->dv.ks);
+    B.max_update = ub > B.max_update ? ub : B.max_update;
   }
   if (amap) {
     // workgroups start in table order: the longest tours' ants first, so that
@@ -1107,8 +1094,6 @@ static void batch_shape(faco_instance *const *hs, int32_t count, Inst *insts, in
 static void enqueue_batch_iteration(const BatchShape &B, const Inst *d_insts,
                                     const int2 *d_amap, hipStream_t s) {
   const unsigned nb_ant = (unsigned)((B.total + B.apb - 1) / B.apb);
-  const dim3 g_src((unsigned)((B.maxn + 255) / 256), (unsigned)B.count);
-  const dim3 g_tau((unsigned)((B.max_slots + 255) / 256), (unsigned)B.count);
   hipLaunchKernelGGL(B.antk, dim3(nb_ant), dim3(64 * (B.tw > 1 ? B.tw : B.apb)), B.lds_bytes,
                      s, d_insts, d_amap, B.total, B.apb, (int)B.lds_words);
   if (B.any_verify) {
@@ -1119,10 +1104,8 @@ static void enqueue_batch_iteration(const BatchShape &B, const Inst *d_insts,
     hipLaunchKernelGGL(faco::verify_finish_batch_kernel, dim3((unsigned)B.count),
                        dim3(faco::kVerifyBlock), 0, s, d_insts);
   }
-  hipLaunchKernelGGL(faco::colony_batch_kernel, dim3((unsigned)B.count), dim3(64), 0, s,
-                     d_insts);
-  hipLaunchKernelGGL(faco::source_batch_kernel, g_src, dim3(256), 0, s, d_insts);
-  hipLaunchKernelGGL(faco::pheromone_batch_kernel, g_tau, dim3(256), 0, s, d_insts);
+  hipLaunchKernelGGL(faco::update_batch_kernel, dim3(B.max_update, (unsigned)B.count),
+                     dim3(faco::kUpdateBlock), 0, s, d_insts);
 }
 
 // Grow a workspace array (the previous batch on the stream has finished, so

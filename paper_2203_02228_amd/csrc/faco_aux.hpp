@@ -1,5 +1,5 @@
-// faco_aux.hpp -- per-iteration colony, source and pheromone kernels, the
-// batched forms of those, and the candidate/backup list builder (gfx950).
+// faco_aux.hpp -- the per-iteration update kernel and its batched form, the
+// tour-length verification and the candidate/backup list builder (gfx950).
 #pragma once
 #include "device_common.hpp"
 #include "faco_device.hpp"
@@ -7,14 +7,17 @@
 
 namespace faco {
 
-__global__ void __launch_bounds__(64) colony_kernel(Inst I) { run_colony(I); }
-
-__global__ void __launch_bounds__(256) source_kernel(Inst I, int init) {
-  run_source(I, (int)(blockIdx.x * blockDim.x + threadIdx.x), init);
+__global__ void __launch_bounds__(kUpdateBlock) update_kernel(Inst I) {
+  run_update(I, blockIdx.x);
 }
 
-__global__ void __launch_bounds__(256) pheromone_kernel(Inst I, int init) {
-  run_pheromone(I, blockIdx.x * blockDim.x + threadIdx.x, init);
+// Source and pheromone before the first iteration.
+__global__ void __launch_bounds__(256) init_source_kernel(Inst I) {
+  run_source(I, (int)(blockIdx.x * blockDim.x + threadIdx.x), 1);
+}
+
+__global__ void __launch_bounds__(256) init_pheromone_kernel(Inst I) {
+  run_pheromone(I, blockIdx.x * blockDim.x + threadIdx.x, 1);
 }
 
 // Limits of the initial solution; state before the first iteration.
@@ -113,17 +116,10 @@ __host__ __device__ inline unsigned verify_chunks(int n) {
 // Batched forms: blockIdx selects the instance; each instance reads only
 // its own Inst.
 // ===================================================================== //
-__global__ void __launch_bounds__(64) colony_batch_kernel(const Inst *insts) {
-  run_colony(insts[blockIdx.x]);
-}
-
-// blockIdx.y = instance; blocks past an instance's size return
-__global__ void __launch_bounds__(256) source_batch_kernel(const Inst *insts) {
-  run_source(insts[blockIdx.y], (int)(blockIdx.x * blockDim.x + threadIdx.x), 0);
-}
-
-__global__ void __launch_bounds__(256) pheromone_batch_kernel(const Inst *insts) {
-  run_pheromone(insts[blockIdx.y], blockIdx.x * blockDim.x + threadIdx.x, 0);
+// blockIdx.y = instance; blocks past an instance's own return
+__global__ void __launch_bounds__(kUpdateBlock) update_batch_kernel(const Inst *insts) {
+  const Inst &I = insts[blockIdx.y];
+  if (blockIdx.x < update_blocks(I.n, I.ks)) run_update(I, blockIdx.x);
 }
 
 // blockIdx.z = instance; instances without verification, and tours or

@@ -26,6 +26,7 @@ struct DevState {
   // has ended.
   int64_t init_cur, init_clock;
   int32_t init_changes, init_done;
+  int32_t updates, pad1;  // blocks of the update that have read the state
   int64_t fault_iter;
   int64_t verified;
 };
@@ -77,7 +78,7 @@ struct Inst {
   const float *eta;
   const int32_t *cl_d;  // [n][k] cost of every candidate slot
   float *tau;
-  int32_t *src_route, *src_pos, *gb_route;
+  int32_t *src_route, *src_pos, *gb_route, *gb_pos;
   int2 *src_adj;      // [n] (successor, predecessor) of each city in the source
   // Candidate rows in SOURCE order (row p = candidates of the city at source
   // position p), rewritten by the pheromone kernel every iteration; laid out
