@@ -345,6 +345,14 @@ FACO_DEV void queue_take(const TeamLds *tl, Queue &Q) {
   Q.in_lds = team_arg(tl, 4);
 }
 
+// Cities per wave up to which a sweep evaluates them one after the other, each
+// by a whole wave (0.7 us a city), instead of 64 at once, a lane each (10 to 13
+// us a step, up to four dependent chunks of candidates).  Sweeps of the slowest
+// ant per iteration, in us: 35 cities (200-city tours) 7.2 against 24.8, 123
+// (1000) 31 against 36.  Thresholds 8/16/32/64 give iterations of 1000 cities
+// in 257/248/246/246 us and of 5000 in 582/581/581/591.
+constexpr int kWaveSweep = 32;
+
 // Sweep by all waves (see sweep()): the touched cities are gathered into a
 // list in LDS (the queue's ring, empty during a sweep; all of them at once
 // when they fit, else a range of bitmap words at a time), every wave tests 64
@@ -353,7 +361,8 @@ FACO_DEV void queue_take(const TeamLds *tl, Queue &Q) {
 template <int KT, int TW>
 FACO_DEV int team_sweep(const Inst &I, uint32_t flags, int W, Queue &Q, const FlatT &T,
                         uint32_t *inq, uint32_t *touched, uint32_t *ord, TeamLds *tl, int w,
-                        LaneCounters &tk) {
+                        const TeamLane &tlane, LaneCounters &tk) {
+  constexpr int GS = KT <= 16 ? 16 : 32;
   const int lane = lane_id(), tid = w * kWave + lane;
   constexpr int NT = TW * kWave;
   const int64_t t0 = ticks();
@@ -396,12 +405,27 @@ FACO_DEV int team_sweep(const Inst &I, uint32_t flags, int W, Queue &Q, const Fl
     }
     team_sync();
     const int cnt = uniform_i(tl->ls.cnt[p]);
-    for (int i0 = w * kWave; i0 < cnt; i0 += NT) {
-      const int i = i0 + lane;
-      if (i < cnt) {
-        const int x = list[i];
+    if (cnt <= kWaveSweep * TW) {
+      int x = w < cnt ? uniform_i(list[w]) : 0;
+      TeamPre P = team_pre<GS>(I, x);
+      for (int i = w; i < cnt; i += TW) {
+        const int xn = i + TW < cnt ? uniform_i(list[i + TW]) : x;
+        const TeamPre Pn = team_pre<GS>(I, xn);
         const int ox = I.orig_of[x];
-        if (has_improving<KT>(I, flags, x, T)) bit_set(ord, ox);
+        if (team_eval<GS>(I, tlane, P, T.route, T.pos, T.rxy, tl->ls.desc[0] + w * kDescWords) > 0 &&
+            lane == 0)
+          bit_set(ord, ox);
+        x = xn;
+        P = Pn;
+      }
+    } else {
+      for (int i0 = w * kWave; i0 < cnt; i0 += NT) {
+        const int i = i0 + lane;
+        if (i < cnt) {
+          const int x = list[i];
+          const int ox = I.orig_of[x];
+          if (has_improving<KT>(I, flags, x, T)) bit_set(ord, ox);
+        }
       }
     }
     team_sync();
@@ -635,7 +659,7 @@ FACO_DEV int64_t team_local_search(const Inst &I, uint32_t flags, int32_t *route
     changes_at_sweep = changes;
     ++sweeps;
     const int pushed = uniform_i(team_sweep<KT, TW>(I, flags, W, Q, FlatT{route, pos, rxy}, inq,
-                                                    touched, ord, tl, w, tk));
+                                                    touched, ord, tl, w, tlane, tk));
     pre_a = -1;
     if (w == 0) {
       const int64_t t1 = ticks();
