@@ -193,6 +193,12 @@ FACO_DEV T &at(T *base, int i) {
   return *(T *)((B *)base + (uint32_t)i * (uint32_t)sizeof(T));
 }
 
+// The element at a byte offset from a wave-uniform address.
+template <class T>
+FACO_DEV const T &at_byte(const T *base, uint32_t off) {
+  return *(const T *)((const char *)base + off);
+}
+
 // --------------------------------------------------------------- bitmap ---
 
 FACO_DEV bool bit_get(const uint32_t *bm, int x) {

@@ -274,45 +274,63 @@ FACO_DEV void mark_run(uint32_t *vis, int p, int L, int n) {
 }
 
 // Append J consecutive source positions, the first at pcur + dir, at tour
-// positions k on: wave w's share.  Returns its part of their edge costs.
+// positions k on: wave w's share; the edge costs go to the lanes' sums.  The
+// next positions are loaded before the present ones are stored, so a wave
+// always has loads in flight (a copy is bound by the latency of what one CU
+// keeps in flight: 193k cities in 195 us load-then-store, 8 a lane).
 template <int TW>
-FACO_DEV int64_t copy_part(const Inst &I, int pcur, int dir, int k, int J, int w, int32_t *route,
-                           int32_t *pos, int2 *rxy) {
+FACO_DEV void copy_part(const Inst &I, int pcur, int dir, int k, int J, int w, int32_t *route,
+                        int32_t *pos, int2 *rxy, int64_t &lane_len) {
   const int n = I.n, lane = lane_id();
-  constexpr int CH = 8;  // positions per lane in flight
-  int64_t sum = 0;
-  for (int i0 = w * CH * kWave; i0 < J; i0 += TW * CH * kWave) {
-    int cc[CH], dd[CH], cx[CH], cy[CH];
+  constexpr int CH = 4;  // positions per lane and step
+  constexpr int STEP = TW * CH * kWave;
+  struct Buf {
+    int c[CH], d[CH], x[CH], y[CH];
+  };
+  auto load = [&](int i0, Buf &B) {
 #pragma unroll
     for (int h = 0; h < CH; ++h) {
       const int i = i0 + h * kWave + lane;
       if (i < J) {
         const int q = wrapc(pcur + dir * (i + 1), n);
-        cc[h] = at(I.src_route, q);
+        B.c[h] = at(I.src_route, q);
         const int2 x = at(I.src_xy, q);
-        cx[h] = x.x;
-        cy[h] = x.y;
-        dd[h] = at(I.src_d, dir > 0 ? (q == 0 ? n - 1 : q - 1) : q);
+        B.x[h] = x.x;
+        B.y[h] = x.y;
+        B.d[h] = at(I.src_d, dir > 0 ? (q == 0 ? n - 1 : q - 1) : q);
       }
     }
+  };
+  auto store = [&](int i0, const Buf &B) {
 #pragma unroll
     for (int h = 0; h < CH; ++h) {
       const int i = i0 + h * kWave + lane;
       if (i < J) {
-        at(route, k + i) = cc[h];
-        at(rxy, k + i) = make_int2(cx[h], cy[h]);
-        at(pos, cc[h]) = k + i;
-        sum += dd[h];
+        at(route, k + i) = B.c[h];
+        at(rxy, k + i) = make_int2(B.x[h], B.y[h]);
+        at(pos, B.c[h]) = k + i;
+        lane_len += B.d[h];
       }
     }
+  };
+  Buf A, B;
+  int i0 = w * CH * kWave;
+  if (i0 < J) load(i0, A);
+  while (i0 < J) {
+    if (i0 + STEP < J) load(i0 + STEP, B);
+    store(i0, A);
+    i0 += STEP;
+    if (i0 >= J) break;
+    if (i0 + STEP < J) load(i0 + STEP, A);
+    store(i0, B);
+    i0 += STEP;
   }
-  return wave_sum_i64(sum);
 }
 
 // Copy-from-source (Alg. 2, reading: forward from pv while unvisited, else
 // backward).  Returns the count; pu becomes the last appended position.
 template <int TW>
-FACO_DEV int copy_from(const Inst &I, int pv, int &k, int &pu, int64_t &len, TeamLds *tl,
+FACO_DEV int copy_from(const Inst &I, int pv, int &k, int &pu, int64_t &lane_len, TeamLds *tl,
                        int32_t *route, int32_t *pos, int2 *rxy, uint32_t *vis) {
   const int n = I.n;
   int dir = 1;
@@ -323,17 +341,16 @@ FACO_DEV int copy_from(const Inst &I, int pv, int &k, int &pu, int64_t &len, Tea
     if (J == 0) return 0;
   }
   // short runs are the leader's alone
-  if (TW > 1 && J > 8 * kWave) {
+  const bool team = TW > 1 && J > 8 * kWave;
+  if (team) {
     team_post(tl, OP_COPY, pv, dir, k, J);
-    tl->part[0] = copy_part<TW>(I, pv, dir, k, J, 0, route, pos, rxy);
-    mark_run(vis, dir > 0 ? wrapc(pv + 1, n) : wrapc(pv - J, n), J, n);
-    team_sync();
-    len += wave_sum_i64(lane_id() < TW ? tl->part[lane_id()] : 0);
+    copy_part<TW>(I, pv, dir, k, J, 0, route, pos, rxy, lane_len);
   } else {
-    len += copy_part<1>(I, pv, dir, k, J, 0, route, pos, rxy);
-    mark_run(vis, dir > 0 ? wrapc(pv + 1, n) : wrapc(pv - J, n), J, n);
-    wave_fence();
+    copy_part<1>(I, pv, dir, k, J, 0, route, pos, rxy, lane_len);
   }
+  mark_run(vis, dir > 0 ? wrapc(pv + 1, n) : wrapc(pv - J, n), J, n);
+  if (team) team_sync();
+  wave_fence();
   k += J;
   pu = wrapc(pv + dir * J, n);
   return J;
@@ -373,7 +390,6 @@ struct WinOut {
   int acc;        // steps that followed the source
   int pv;         // choice of step `step + acc` (-2: window ran out, -1: no
                   // candidate is unvisited)
-  int64_t srcsum; // costs of the followed edges
 };
 
 // Waves that evaluate a window (64 steps each): one per SIMD of a CU.  A
@@ -390,7 +406,8 @@ constexpr bool cached_draws() { return TW > win_waves<TW>(); }
 template <int KT, int TW>
 FACO_DEV void window_part(const Inst &I, uint64_t t, uint64_t ant, int step, int pu, int dir,
                           int k, int w, int &have, TeamLds *tl, const uint32_t *vis,
-                          int32_t *route, int32_t *pos, int2 *rxy, WinOut &o, int round = 0) {
+                          int32_t *route, int32_t *pos, int2 *rxy, int64_t &lane_len, WinOut &o,
+                          int round = 0) {
   constexpr int WW = win_waves<TW>();
   const int n = I.n, K4 = I.ks, lane = lane_id();
   const int g = w * kWave + lane;
@@ -482,14 +499,13 @@ FACO_DEV void window_part(const Inst &I, uint64_t t, uint64_t ant, int step, int
   const int acc = F < valid ? F : valid;
   o.acc = acc;
   o.pv = -2;
-  o.srcsum = 0;
   if (w < WW) {
     if (g < acc) {
       at(route, k + g) = qn;
       at(rxy, k + g) = qxy;
       at(pos, qn) = k + g;
+      lane_len += ed;
     }
-    o.srcsum = wave_sum_i64(g < acc ? (int64_t)ed : 0);
     if (acc < valid) {
       if (TW == 1)
         o.pv = readlane_i(choice, acc);
@@ -503,17 +519,16 @@ FACO_DEV void window_part(const Inst &I, uint64_t t, uint64_t ant, int step, int
 // A team runs up to kWinRounds windows in one command: while a window is
 // followed to its end, the next one starts from where it stopped (every wave
 // derives the new start alike).  Wave 0 marks the followed positions between
-// barriers.  Per-wave sums of the followed edges end in tl->part; o.acc is the
-// total.
+// barriers.  The followed edges' costs go to the lanes' sums; o.acc is the total.
+// The command ends at its last round's barrier.
 constexpr int kWinRounds = 32;
 template <int KT, int TW>
 FACO_DEV void window_rounds(const Inst &I, uint64_t t, uint64_t ant, int step, int pu, int dir,
                             int k, int w, int &have, TeamLds *tl, uint32_t *vis, int32_t *route,
-                            int32_t *pos, int2 *rxy, WinOut &o) {
+                            int32_t *pos, int2 *rxy, int64_t &lane_len, WinOut &o) {
   constexpr int NW = win_waves<TW>() * kWave;
   const int n = I.n;
   int total = 0;
-  int64_t sum = 0;
   if (cached_draws<TW>() && have < step + NW) {
     // the first window, or a restart behind one-step choices
     have = step;
@@ -523,10 +538,10 @@ FACO_DEV void window_rounds(const Inst &I, uint64_t t, uint64_t ant, int step, i
   }
   for (int r = 0;; ++r) {
     WinOut q;
-    window_part<KT, TW>(I, t, ant, step, pu, dir, k, w, have, tl, vis, route, pos, rxy, q, r);
+    window_part<KT, TW>(I, t, ant, step, pu, dir, k, w, have, tl, vis, route, pos, rxy,
+                        lane_len, q, r);
     const int acc = uniform_i(q.acc);
     total += acc;
-    sum += q.srcsum;
     if (w == 0 && acc > 0)
       mark_run(vis, dir > 0 ? wrap_off(pu, 1, n) : wrap_off(pu, -acc, n), acc, n);
     const int valid = n - k < NW ? n - k : NW;
@@ -540,28 +555,27 @@ FACO_DEV void window_rounds(const Inst &I, uint64_t t, uint64_t ant, int step, i
     step += acc;
   }
   o.acc = total;
-  if (lane_id() == 0) tl->part[w] = sum;
 }
 
 // Leader side of a window (TW > 1: posts it, takes wave 0's share, collects).
 template <int KT, int TW>
 FACO_DEV WinOut team_window(const Inst &I, uint64_t t, uint64_t ant, int step, int pu, int dir,
                             int k, int &have, TeamLds *tl, uint32_t *vis, int32_t *route,
-                            int32_t *pos, int2 *rxy) {
+                            int32_t *pos, int2 *rxy, int64_t &lane_len) {
   WinOut o;
   if (TW == 1) {
-    window_part<KT, TW>(I, t, ant, step, pu, dir, k, 0, have, tl, vis, route, pos, rxy, o);
+    window_part<KT, TW>(I, t, ant, step, pu, dir, k, 0, have, tl, vis, route, pos, rxy, lane_len,
+                        o);
     if (o.acc > 0)
       mark_run(vis, dir > 0 ? wrap_off(pu, 1, I.n) : wrap_off(pu, -o.acc, I.n), o.acc, I.n);
     return o;
   }
   if (lane_id() == 0) tl->arg64[0] = t;
   team_post(tl, OP_WINDOW, pu, dir, k, step, have);
-  window_rounds<KT, TW>(I, t, ant, step, pu, dir, k, 0, have, tl, vis, route, pos, rxy, o);
-  team_sync();
+  window_rounds<KT, TW>(I, t, ant, step, pu, dir, k, 0, have, tl, vis, route, pos, rxy,
+                        lane_len, o);
   o.acc = uniform_i(o.acc);
   have = uniform_i(have);
-  o.srcsum = wave_sum_i64(lane_id() < win_waves<TW>() ? tl->part[lane_id()] : 0);
   o.pv = uniform_i(o.pv) == 0 ? uniform_i(tl->res[1]) : -2;
   return o;
 }
@@ -632,7 +646,7 @@ FACO_DEV int64_t construct(const Inst &I, uint64_t t, int ant, int32_t *route, i
   m = uniform_i(m);
   int k = 1, new_edges = 0, dir = 1;
   nchk = 0;
-  int64_t len = 0;
+  int64_t len = 0, lane_len = 0;  // edge costs: of single steps, of runs by lane
   int step = 0, have = 0;
   Draws D;
   D.base = -1;
@@ -657,14 +671,13 @@ FACO_DEV int64_t construct(const Inst &I, uint64_t t, int ant, int32_t *route, i
     } else {
       // accepted steps follow the source, appended at k on
       const WinOut o = team_window<KT, TW>(I, t, (uint64_t)ant, step, pu, dir, k, have, tl, vis,
-                                           route, pos, rxy);
+                                           route, pos, rxy, lane_len);
       tk[5]++;
       tk[8] += fine_ticks() - c0;
       const int acc = uniform_i(o.acc);
       pv = uniform_i(o.pv);
       k += acc;
       step += acc;
-      len += o.srcsum;
       pu = wrapc(pu + dir * acc, n);
       wave_fence();
     }
@@ -704,13 +717,20 @@ FACO_DEV int64_t construct(const Inst &I, uint64_t t, int ant, int32_t *route, i
     dir = uniform_i(dir);
     if (new_edges >= m && k < n) {
       const int64_t c2 = fine_ticks();
-      const int app = copy_from<TW>(I, pv, k, pu, len, tl, route, pos, rxy, vis);
+      const int app = copy_from<TW>(I, pv, k, pu, lane_len, tl, route, pos, rxy, vis);
       cnt[CNT_COPIED] += app;
       tk[7]++;
       tk[10] += fine_ticks() - c2;
     }
   }
   len += cost(I.src_xy[pu], x0);
+  len += wave_sum_i64(lane_len);
+  if (TW > 1) {
+    // the helpers' sums
+    team_post(tl, OP_LENGTH);
+    team_sync();
+    len += wave_sum_i64(lane > 0 && lane < TW ? tl->part[lane] : 0);
+  }
   cnt[CNT_ACO_STEPS] += step;
   cnt[CNT_NEW_EDGES] += new_edges;
   wave_fence();

@@ -89,7 +89,7 @@ FACO_DEV int wrap_off(int q, int off, int n) {
 // ===================================================================== //
 constexpr int kMaxTeam = 8;
 enum TeamOp {
-  OP_EXIT, OP_WINDOW, OP_SWEEP, OP_COPY, OP_NEAREST, OP_NEAREST_LABEL, OP_OROPT, OP_SEGPERM, OP_SEGMAT, OP_SEARCH
+  OP_EXIT, OP_WINDOW, OP_SWEEP, OP_COPY, OP_LENGTH, OP_NEAREST, OP_NEAREST_LABEL, OP_OROPT, OP_SEGPERM, OP_SEGMAT, OP_SEARCH
 };
 constexpr int kDraws = 1024;     // a power of two
 constexpr int kDescWords = 36;  // a wave's move record in the team local search
@@ -1214,6 +1214,7 @@ FACO_DEV int64_t local_search(const Inst &I, uint32_t flags, int32_t *route,
 template <int KT, int TW, bool SEG>
 FACO_DEV int team_helper(const Inst &I, int ant, int w, TeamLds *tl, uint32_t *vis,
                           uint32_t *ord, int32_t *route, int32_t *pos, int2 *rxy, int4 *rec) {
+  int64_t lane_len = 0;  // costs of the edges this wave's lanes appended
   // a segment-list move's record whose cities this wave labels after the move
   int rl_h = -1, rl_lo = 0, rl_hi = -1;
   SegT rl_T;
@@ -1230,10 +1231,13 @@ FACO_DEV int team_helper(const Inst &I, int ant, int w, TeamLds *tl, uint32_t *v
       int have = team_arg(tl, 4);
       window_rounds<KT, TW>(I, uniform_u64(tl->arg64[0]), (uint64_t)ant, team_arg(tl, 3),
                             team_arg(tl, 0), team_arg(tl, 1), team_arg(tl, 2), w, have, tl, vis,
-                            route, pos, rxy, o);
+                            route, pos, rxy, lane_len, o);
+      continue;  // the command ended at its own last barrier
     } else if (op == OP_COPY) {
-      const int64_t sum = copy_part<TW>(I, team_arg(tl, 0), team_arg(tl, 1), team_arg(tl, 2),
-                                        team_arg(tl, 3), w, route, pos, rxy);
+      copy_part<TW>(I, team_arg(tl, 0), team_arg(tl, 1), team_arg(tl, 2), team_arg(tl, 3), w,
+                    route, pos, rxy, lane_len);
+    } else if (op == OP_LENGTH) {
+      const int64_t sum = wave_sum_i64(lane_len);
       if (lane_id() == 0) tl->part[w] = sum;
     } else if (op == OP_NEAREST || op == OP_NEAREST_LABEL) {
       int64_t md;

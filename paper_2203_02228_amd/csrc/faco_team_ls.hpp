@@ -116,29 +116,34 @@ FACO_DEV int team_eval(const Inst &I, const TeamLane &T, const TeamPre &P,
   // level 2: a's neighbourhood and b's neighbour
   const int32_t *rb = route + (pa - 3);
   const int2 *xr = rxy + (pa - 3);
-  int ju = T.su, jv = T.sv, ja = T.ja, jb = T.jb, jc = T.jc;
-  if (pa < 3 || pa + 3 >= n) {
+  uint32_t ou = 8u * (uint32_t)T.su, ov = 8u * (uint32_t)T.sv;
+  uint32_t oa = 8u * (uint32_t)T.ja, ob = 8u * (uint32_t)T.jb, oc = 8u * (uint32_t)T.jc;
+  int pbn = pb + T.step;
+  pbn = pbn == n ? 0 : pbn;
+  pbn = (int)min((uint32_t)pbn, (uint32_t)(n - 1));  // -1: the last position
+  // which of the positions pa - 3 + j hold b and bn (rj, rn; others: any
+  // value outside 0..6, kept apart by the shift's 31)
+  int rj = pb - pa + 3, rn = rj + T.step;
+  uint32_t wrap_bits = 0u;
+  if (pa < 8 || pa + 8 >= n) {
     rb = route;
     xr = rxy;
-    ju = wrapc(pa - 3 + ju, n);
-    jv = wrapc(pa - 3 + jv, n);
-    ja = wrapc(pa - 3 + ja, n);
-    jb = wrapc(pa - 3 + jb, n);
-    jc = wrapc(pa - 3 + jc, n);
+    ou = 8u * (uint32_t)wrapc(pa - 3 + T.su, n);
+    ov = 8u * (uint32_t)wrapc(pa - 3 + T.sv, n);
+    oa = 8u * (uint32_t)wrapc(pa - 3 + T.ja, n);
+    ob = 8u * (uint32_t)wrapc(pa - 3 + T.jb, n);
+    oc = 8u * (uint32_t)wrapc(pa - 3 + T.jc, n);
+    rj = wrapc(rj, n);
+    rn = wrapc(rj + T.step, n);
+    if (n < 7)  // a tour shorter than the neighbourhood
+      wrap_bits = (1u << (rj + n)) | (1u << (rn + n));
   }
-  const int2 U = at(xr, ju), V = at(xr, jv);
-  const int nb = at(rb, ju);
-  const int2 xA = at(xr, ja), xB = at(xr, jb), xC = at(xr, jc);
-  int pbn = pb + T.step;
-  pbn = pbn < 0 ? n - 1 : pbn;
-  pbn = pbn == n ? 0 : pbn;
   const int2 xbn = at(rxy, pbn);
+  const int2 U = at_byte(xr, ou), V = at_byte(xr, ov);
+  const int2 xA = at_byte(xr, oa), xB = at_byte(xr, ob), xC = at_byte(xr, oc);
   const int bn = at(route, pbn);
-  // which of the positions pa - 3 + j hold b and bn
-  const int rj = wrapc(pb - pa + 3, n);
-  const int rn = wrapc(rj + T.step, n);
-  uint32_t M = (1u << (rj < 31 ? rj : 31)) | (1u << (rn < 31 ? rn : 31));
-  if (n < 7) M |= M << n;  // a tour shorter than the neighbourhood
+  const int nb = at_byte(rb, ou >> 1);
+  const uint32_t M = (1u << min((uint32_t)rj, 31u)) | (1u << min((uint32_t)rn, 31u)) | wrap_bits;
   const int uc = cost_ne(U, V);
   const int in = cost_ne(xb, xbn) - d_ab;  // edge freed at b minus the new edge (a, b)
   int u[11];
@@ -502,10 +507,10 @@ FACO_DEV int64_t team_local_search(const Inst &I, uint32_t flags, int32_t *route
       }
       team_sync();
       // lanes 2 v and 2 v + 1 hold the head of wave v's record
-      int4 v = make_int4(0, 0, 0, 0);
-      if (lane < 2 * gcount)
-        v = reinterpret_cast<const int4 *>(desc)[(lane >> 1) * (kDescWords / 4) + (lane & 1)];
-      const uint64_t hm = ballot((lane & 1) == 0 && v.x > 0);
+      // (the records of waves without a city are old ones)
+      const int vl = lane & (2 * TW - 1);
+      const int4 v = reinterpret_cast<const int4 *>(desc)[(vl >> 1) * (kDescWords / 4) + (vl & 1)];
+      const uint64_t hm = ballot(v.x > 0) & 0x5555u & ((1u << (2 * gcount)) - 1u);
       const int j = uniform_i(hm ? ctz64(hm) >> 1 : gcount);
       const int npop = j < gcount ? j + 1 : gcount;
       // wave 0 unlists the popped cities
