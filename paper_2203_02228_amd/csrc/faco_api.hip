@@ -198,10 +198,6 @@ static int dalloc(faco_instance *h, void **ptr, size_t bytes) {
   return FACO_OK;
 }
 
-static size_t knn_lds_bytes(int K, int BL) {
-  return (sizeof(double) + sizeof(int32_t)) * (size_t)(K + BL) * 64;
-}
-
 static hipEvent_t take_event(faco_instance *h) {
   hipEvent_t e = nullptr;
   if (!h->ev_pool.empty()) {
@@ -598,14 +594,11 @@ extern "C" int faco_build_instance(const int32_t *xy, int32_t n, const faco_para
   BTRY(hipMemcpyAsync((void *)I.int_of, h->int_of.data(), sizeof(int32_t) * N,
                       hipMemcpyHostToDevice, h->stream));
 
-  const size_t klds = knn_lds_bytes(h->k, h->bl);
-  BTRY(hipFuncSetAttribute((const void *)faco::knn_kernel,
-                           hipFuncAttributeMaxDynamicSharedMemorySize, (int)klds));
-  hipLaunchKernelGGL(faco::knn_kernel, dim3((unsigned)((n + 63) / 64)), dim3(64), klds,
-                     h->stream, I.xy, I.orig_of, I.int_of, I.wbox, n, h->k, h->bl,
-                     (int32_t *)I.cl,
-                     (int32_t *)I.bll,
-                     (float *)I.eta, (int32_t *)I.cl_d, I.st);
+  hipLaunchKernelGGL(faco::knn_kernel,
+                     dim3((unsigned)((n + faco::kKnnWaves - 1) / faco::kKnnWaves)),
+                     dim3(faco::kWave * faco::kKnnWaves), 0, h->stream, I.xy, I.orig_of, I.int_of,
+                     I.wbox, n, h->k, h->bl, (int32_t *)I.cl, (int32_t *)I.bll, (float *)I.eta,
+                     (int32_t *)I.cl_d, I.st);
   BTRY(hipGetLastError());
   DevState hs;
   BTRY(hipMemcpyAsync(&hs, I.st, sizeof(DevState), hipMemcpyDeviceToHost, h->stream));
