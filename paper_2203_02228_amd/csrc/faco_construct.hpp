@@ -740,8 +740,13 @@ FACO_DEV int64_t construct(const Inst &I, uint64_t t, int ant, int32_t *route, i
 // ===================================================================== //
 // The nearest-neighbour tour from city 0 (initial solution), by labels: first
 // unvisited candidate (lists are sorted by distance), else the fallback chain.
-// The chain of one step is a candidate row's load and its visited bits;
-// positions, coordinates and the length follow in one pass over the tour.
+// The chain of one step is a candidate row's load and its visited bits.  A load
+// is waited for behind every memory operation issued before it, so nothing is
+// stored per step (64 cities leave together), and the rows of the present
+// city's candidates are touched after the next row's own load: the next steps'
+// rows then come from the CU's L1.  A build of 20000 cities went from 26.9 to
+// 25.4 ms with both, of 200000 from 394 to 381 ms.  Positions, coordinates and
+// the length follow in one pass over the tour.
 // ===================================================================== //
 template <int TW>
 FACO_DEV int64_t construct_greedy(const Inst &I, int32_t *route, int32_t *pos, int2 *rxy,
@@ -754,12 +759,11 @@ FACO_DEV int64_t construct_greedy(const Inst &I, int32_t *route, int32_t *pos, i
   }
   wave_fence();
   int u = uniform_i(I.int_of[0]);
-  if (lane == 0) {
-    route[0] = u;
-    bit_set(vis, u);
-  }
+  if (lane == 0) bit_set(vis, u);
+  int held = u;            // lane l: city 64 j + l of the tour, j the present group
+  int c = lane < K ? at(I.cl, u * K + lane) : 0;
+  int touch = 0, sink = 0;
   for (int k = 1; k < n; k = uniform_i(k + 1)) {
-    const int c = lane < K ? at(I.cl + (size_t)u * (size_t)K, lane) : 0;
     const uint64_t um = ballot(lane < K && !bit_get(vis, c));
     int v;
     if (um) {
@@ -781,11 +785,20 @@ FACO_DEV int64_t construct_greedy(const Inst &I, int32_t *route, int32_t *pos, i
       }
     }
     u = uniform_i(v);
-    if (lane == 0) {
-      at(route, k) = u;
-      bit_set(vis, u);
-    }
+    const int row = c;
+    if (lane < K) c = at(I.cl, u * K + lane);
+    if (lane == 0) bit_set(vis, u);
+    sink ^= touch;
+    if (lane < K) touch = at(I.cl, row * K + (K >> 1));
+    if ((k & (kWave - 1)) == 0) at(route, k - kWave + lane) = held;
+    held = lane == (k & (kWave - 1)) ? u : held;
   }
+  {
+    const int first = (n - 1) & ~(kWave - 1);
+    if (first + lane < n) at(route, first + lane) = held;
+  }
+  // (never so: city numbers are below 2^18)
+  if (sink == -1) bit_set(inq, 0);
   wave_fence();
   int64_t len = 0;
   for (int i0 = 0; i0 < n; i0 += 4 * kWave) {
