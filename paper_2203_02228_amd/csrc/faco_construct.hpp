@@ -738,16 +738,56 @@ FACO_DEV int64_t construct(const Inst &I, uint64_t t, int ant, int32_t *route, i
 }
 
 // ===================================================================== //
+// Wave 1 of a team while wave 0 builds the nearest-neighbour tour: the rows of
+// the candidates of the candidates of the city that wave 0 is at (tl->arg[0])
+// are brought into the CU's L1 until wave 0 sets tl->arg[1] (which it does
+// before every barrier).  Nothing but time depends on what it reads.  The tour is
+// bound by the latency of one candidate row per city; wave 0's own touches of the
+// rows ahead held its next load up, as loads return in order.  A build of 1000
+// cities went from 1.44 to 1.37 ms, of 20000 from 25.4 to 23.8, of 200000 from
+// 381 to 364 ms against touches by wave 0.
+// ===================================================================== //
+FACO_DEV void greedy_rows(const Inst &I, TeamLds *tl) {
+  const int K = I.k, lane = lane_id();
+  const int s1 = (lane >> 2) < K ? lane >> 2 : K - 1, s2 = (lane & 3) < K ? lane & 3 : K - 1;
+  int last = -1;
+  for (;;) {
+    if (uniform_i(__hip_atomic_load(&tl->arg[1], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP)))
+      return;
+    const int u = uniform_i(
+        __hip_atomic_load(&tl->arg[0], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP));
+    if (u == last) {
+      __builtin_amdgcn_s_sleep(1);
+      continue;
+    }
+    last = u;
+    const int c1 = at(I.cl, u * K + s1);
+    const int c2 = at(I.cl, c1 * K + s2);
+    const int c3 = at(I.cl, c2 * K + (K >> 1));
+    asm volatile("" : : "v"(c3));
+  }
+}
+
+// ===================================================================== //
 // The nearest-neighbour tour from city 0 (initial solution), by labels: first
 // unvisited candidate (lists are sorted by distance), else the fallback chain.
 // The chain of one step is a candidate row's load and its visited bits.  A load
 // is waited for behind every memory operation issued before it, so nothing is
-// stored per step (64 cities leave together), and the rows of the present
-// city's candidates are touched after the next row's own load: the next steps'
-// rows then come from the CU's L1.  A build of 20000 cities went from 26.9 to
-// 25.4 ms with both, of 200000 from 394 to 381 ms.  Positions, coordinates and
-// the length follow in one pass over the tour.
+// stored per step (64 cities leave together), and the rows of the next steps are
+// brought into the CU's L1 beforehand: by another wave (greedy_rows), or, where
+// the ant has one wave only, by touching the rows of the present city's
+// candidates after the next row's own load.  A build of 20000 cities went from
+// 26.9 to 25.4 ms with one wave's touches and without the stores.  Positions,
+// coordinates and the length follow in one pass over the tour.
 // ===================================================================== //
+template <int TW>
+FACO_DEV void greedy_stop(TeamLds *tl) {
+  if (TW == 1) return;
+  if (lane_id() == 0)
+    __hip_atomic_store(&tl->arg[1], 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+  team_sync();
+}
+
 template <int TW>
 FACO_DEV int64_t construct_greedy(const Inst &I, int32_t *route, int32_t *pos, int2 *rxy,
                                   uint32_t *vis, uint32_t *inq, TeamLds *tl, int W,
@@ -763,6 +803,7 @@ FACO_DEV int64_t construct_greedy(const Inst &I, int32_t *route, int32_t *pos, i
   int held = u;            // lane l: city 64 j + l of the tour, j the present group
   int c = lane < K ? at(I.cl, u * K + lane) : 0;
   int touch = 0, sink = 0;
+  if (TW > 1) team_post(tl, OP_GREEDY, u, 0);
   for (int k = 1; k < n; k = uniform_i(k + 1)) {
     const uint64_t um = ballot(lane < K && !bit_get(vis, c));
     int v;
@@ -781,18 +822,27 @@ FACO_DEV int64_t construct_greedy(const Inst &I, int32_t *route, int32_t *pos, i
         v = readlane_i(b, ctz64(bm));
       } else {
         cnt[CNT_FALLBACK]++;
+        greedy_stop<TW>(tl);
         v = nearest<false, TW>(I, u, vis, tl);
+        if (TW > 1) team_post(tl, OP_GREEDY, v, 0);
       }
     }
     u = uniform_i(v);
     const int row = c;
     if (lane < K) c = at(I.cl, u * K + lane);
-    if (lane == 0) bit_set(vis, u);
-    sink ^= touch;
-    if (lane < K) touch = at(I.cl, row * K + (K >> 1));
+    if (lane == 0) {
+      bit_set(vis, u);
+      if (TW > 1)
+        __hip_atomic_store(&tl->arg[0], u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+    }
+    if (TW == 1) {
+      sink ^= touch;
+      if (lane < K) touch = at(I.cl, row * K + (K >> 1));
+    }
     if ((k & (kWave - 1)) == 0) at(route, k - kWave + lane) = held;
     held = lane == (k & (kWave - 1)) ? u : held;
   }
+  greedy_stop<TW>(tl);
   {
     const int first = (n - 1) & ~(kWave - 1);
     if (first + lane < n) at(route, first + lane) = held;

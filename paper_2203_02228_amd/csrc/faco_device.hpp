@@ -51,8 +51,8 @@ enum : int32_t {
 //   bll       [n][bl]            backup lists
 //   routes,
 //   pos, ring [A][n]             ant tours, their inverses, LS checklist rings
-//   cnt       int64 [A][12]      per-ant counters of the last iteration
-//   cnt_acc   int64 [A][12]      the same summed over all iterations
+//   cnt       int64 [A][13]      per-ant counters of the last iteration
+//   cnt_acc   int64 [A][13]      the same summed over all iterations
 struct Inst {
   int32_t n, k, bl, A, m;
   int32_t ks;         // k rounded up to a multiple of 4: slots of a source-ordered row
@@ -78,10 +78,12 @@ struct Inst {
   const float *eta;
   const int32_t *cl_d;  // [n][k] cost of every candidate slot
   float *tau;
-  int32_t *src_route, *src_pos, *gb_route, *gb_pos;
+  int32_t *src_route, *src_pos;
+  int32_t *gb_route;  // right behind *st, in one block: both are read in one copy
+  int32_t *gb_pos;
   int2 *src_adj;      // [n] (successor, predecessor) of each city in the source
   // Candidate rows in SOURCE order (row p = candidates of the city at source
-  // position p), rewritten by the pheromone kernel every iteration; laid out
+  // position p), rewritten by the update kernel every iteration; laid out
   // by srow() in blocks of 64 positions, ks slots per row (those past k hold
   // weight 0 and the row's own position):
   float *sw;          // tau * eta (Eq. (1) weight)

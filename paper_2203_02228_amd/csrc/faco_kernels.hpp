@@ -1,10 +1,12 @@
 // faco_kernels.hpp -- HIP kernels of the FACO hot path for gfx950.
 //
-// One wavefront (64 lanes) owns one ant: the candidate row of the current city
-// is spread over the lanes, the Eq. (1) cumulative sums are formed lane-wise in
-// slot order, the choice is a ballot, the copy-from-source step and the
-// 2-opt/Or-opt array rewrites move 64 elements per instruction.  Visited and
-// "on the checklist" sets are bitmaps in LDS; tours live in HBM.
+// One workgroup owns one ant: a team of 8 or 4 waves (or one wave, in large
+// batches).  The candidate row of the current city is spread over the lanes, the
+// Eq. (1) cumulative sums are formed lane-wise in slot order, the choice is a
+// ballot.  In the construction wave 0 decides and the others take shares of its
+// wide steps (windows, copies, scans) by command; in the local search every wave
+// runs the same loop (faco_team_ls.hpp).  Visited and "on the checklist" sets are
+// bitmaps in LDS; tours live in HBM.
 #pragma once
 #include "device_common.hpp"
 #include "faco_device.hpp"
@@ -77,19 +79,21 @@ FACO_DEV int wrap_off(int q, int off, int n) {
 }
 
 // ===================================================================== //
-// Ant teams.  An ant may own TW waves of one workgroup.  Wave 0 (the leader)
-// runs every decision of the ant; the other waves wait at a workgroup
-// barrier for a command posted in LDS and take a share of the wide steps:
-// the speculative source-following window (64 TW steps at once), the array
-// rewrites of 2-opt and Or-opt moves, and the move tests of a sweep.  Who
-// computes a step never changes its result.
+// Ant teams.  An ant may own TW waves of one workgroup.  In the construction
+// (and in the local search on segment lists) wave 0, the leader, runs every
+// decision; the other waves wait at a workgroup barrier for a command posted
+// in LDS and take a share of the wide steps: source-following windows, copies,
+// nearest-city scans, and on segment lists the record passes, Or-opt variants
+// and sweep tests.  The local search on flat arrays is run by every wave alike
+// (faco_team_ls.hpp).  Who computes a step never changes its result.
 //   protocol: leader writes op + arguments, barrier; every wave does its
 //   share (a step with a read/write hazard has barriers of its own, taken by
 //   every wave alike); barrier; the leader reads what the op left in LDS.
 // ===================================================================== //
 constexpr int kMaxTeam = 8;
 enum TeamOp {
-  OP_EXIT, OP_WINDOW, OP_SWEEP, OP_COPY, OP_LENGTH, OP_NEAREST, OP_NEAREST_LABEL, OP_OROPT, OP_SEGPERM, OP_SEGMAT, OP_SEARCH
+  OP_EXIT, OP_WINDOW, OP_SWEEP, OP_COPY, OP_LENGTH, OP_NEAREST, OP_NEAREST_LABEL, OP_OROPT,
+  OP_SEGPERM, OP_SEGMAT, OP_SEARCH, OP_GREEDY
 };
 constexpr int kDraws = 1024;     // a power of two
 constexpr int kDescWords = 36;  // a wave's move record in the team local search
@@ -1246,6 +1250,8 @@ FACO_DEV int team_helper(const Inst &I, int ant, int w, TeamLds *tl, uint32_t *v
         nearest_part<true, TW>(I, team_arg(tl, 0), w, vis, tl, md, mj);
       else
         nearest_part<false, TW>(I, team_arg(tl, 0), w, vis, tl, md, mj);
+    } else if (op == OP_GREEDY) {
+      if (w == 1) greedy_rows(I, tl);
     } else if (SEG && op == OP_SWEEP) {
       sweep_part<KT, TW>(I, (uint32_t)team_arg(tl, 1), team_arg(tl, 0), w, tl, ord,
                          seg_view(I, ant, rec, uniform_i(tl->sgs[0]), uniform_i(tl->sgs[1]),
