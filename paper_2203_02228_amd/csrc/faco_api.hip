@@ -693,8 +693,17 @@ extern "C" int faco_run_iterations(faco_instance *h, int32_t iterations) {
 
 // Device-to-host copy on the handle's stream, then wait for it.  (The
 // legacy stream is avoided: another thread may be capturing a batch graph.)
+// While the caller captures the stream the wait refuses the call, so it comes
+// first there: the copy would stay in the graph, and each replay would write to
+// dst.
 static hipError_t d2h(faco_instance *h, void *dst, const void *src, size_t bytes) {
-  hipError_t e = hipMemcpyAsync(dst, src, bytes, hipMemcpyDeviceToHost, h->stream);
+  hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
+  hipError_t e = hipStreamIsCapturing(h->stream, &cs);
+  if (e != hipSuccess || cs != hipStreamCaptureStatusNone) {
+    e = hipStreamSynchronize(h->stream);
+    if (e != hipSuccess) return e;
+  }
+  e = hipMemcpyAsync(dst, src, bytes, hipMemcpyDeviceToHost, h->stream);
   if (e != hipSuccess) return e;
   return hipStreamSynchronize(h->stream);
 }

@@ -1,0 +1,33 @@
+"""Host code of the library on the CPU, against a stand-in for the HIP runtime
+(host_stub.py): what each call enqueues, allocates and launches."""
+import pytest
+
+from tests import host_stub
+
+
+@pytest.fixture(scope="module")
+def stub(tmp_path_factory):
+    return host_stub.build_stub(tmp_path_factory.mktemp("stub"))
+
+
+def test_readback_of_a_capturing_stream_is_refused_before_any_copy(stub):
+    """A copy enqueued on a capturing stream becomes a node of the caller's
+    graph, and every replay would write to memory that the refused call has
+    long given back."""
+    got = host_stub.run(stub, """
+h = build(60)
+whats = range(18)
+S.stub_reset()
+S.stub_set_capturing(1)
+refused = 0
+for call in [lambda: F.faco_get_best_tour(h)] + [lambda w=w: F.faco_debug_get(h, w) for w in whats]:
+    try:
+        call()
+    except F.FacoError as e:
+        refused += e.code == F.FACO_EDEVICE
+copies, ln = S.stub_copies(), S.stub_launch_count()
+S.stub_set_capturing(0)
+F.faco_get_best_tour(h)
+print(json.dumps(dict(refused=refused, copies=copies, launches=ln)))
+""")
+    assert got == {"refused": 19, "copies": 0, "launches": 0}
