@@ -1058,9 +1058,11 @@ struct BatchShape {
 };
 
 // Fill the host tables (insts[count], amap[total ants]) and derive the
-// launch shape from the configuration.  Caller holds g_batch_mu.
+// launch shape from the configuration.  order[count]: the instances by tour
+// length, longest first.  Takes no memory of its own (faco_run_batch_noalloc).
+// Caller holds g_batch_mu.
 static void batch_shape(faco_instance *const *hs, int32_t count, Inst *insts, int2 *amap,
-                        const faco_batch_config &cfg, BatchShape &B) {
+                        int32_t *order, const faco_batch_config &cfg, BatchShape &B) {
   B.count = count;
   for (int32_t i = 0; i < count; ++i) {
     faco_instance *h = hs[i];
@@ -1094,17 +1096,15 @@ static void batch_shape(faco_instance *const *hs, int32_t count, Inst *insts, in
     const unsigned ub = faco::update_blocks(h->n, h->dv.ks);
     B.max_update = ub > B.max_update ? ub : B.max_update;
   }
-  if (amap) {
-    // workgroups start in table order: the longest tours' ants first, so that
-    // the launch does not end on one of them
-    std::vector<int32_t> order((size_t)count);
-    for (int32_t i = 0; i < count; ++i) order[(size_t)i] = i;
-    std::stable_sort(order.begin(), order.end(),
-                     [&](int32_t a, int32_t b) { return hs[a]->n > hs[b]->n; });
-    int w = 0;
-    for (int32_t i : order)
-      for (int a = 0; a < hs[i]->p.n_ants; ++a) amap[w++] = make_int2(i, a);
-  }
+  // workgroups start in table order: the longest tours' ants first, so that
+  // the launch does not end on one of them
+  for (int32_t i = 0; i < count; ++i) order[i] = i;
+  std::sort(order, order + count, [&](int32_t a, int32_t b) {
+    return hs[a]->n != hs[b]->n ? hs[a]->n > hs[b]->n : a < b;
+  });
+  int w = 0;
+  for (int32_t j = 0; j < count; ++j)
+    for (int a = 0; a < hs[order[j]]->p.n_ants; ++a) amap[w++] = make_int2(order[j], a);
   // with one wave per ant, ants per workgroup: the configured number,
   // lowered until their LDS fits a CU
   B.apb = B.tw > 1 ? 1 : cfg.ants_per_block;
@@ -1169,8 +1169,9 @@ static int run_batch_one(faco_instance *const *hs, int32_t count, int32_t iterat
   // host tables
   std::vector<Inst> insts((size_t)count);
   std::vector<int2> amap((size_t)batch_ant_count(hs, count));
+  std::vector<int32_t> order((size_t)count);
   BatchShape B;
-  batch_shape(hs, count, insts.data(), amap.data(), cfg, B);
+  batch_shape(hs, count, insts.data(), amap.data(), order.data(), cfg, B);
   const int total = B.total;
   // the tables are shared: the previous batch must be done with them
   if (!g_ws.last_done) BT(hipEventCreateWithFlags(&g_ws.last_done, hipEventDisableTiming));
@@ -1199,10 +1200,6 @@ static int run_batch_one(faco_instance *const *hs, int32_t count, int32_t iterat
   }
   if (B.persistent) {
     // largest tours first: their ants are the longest chains
-    std::vector<int> order((size_t)count);
-    for (int32_t i = 0; i < count; ++i) order[(size_t)i] = i;
-    std::stable_sort(order.begin(), order.end(),
-                     [&](int a, int b) { return hs[a]->n > hs[b]->n; });
     std::vector<Inst> sorted((size_t)count);
     std::vector<faco::BatchCtl> ctl((size_t)count);
     for (int32_t j = 0; j < count; ++j) {
@@ -1552,6 +1549,7 @@ static int scratch_address(int dev, unsigned char **out) {
 // host staging of the tables (guarded by g_batch_mu)
 static Inst g_na_insts[kNoAllocMaxInstances];
 static int2 g_na_amap[kNoAllocMaxAnts];
+static int32_t g_na_order[kNoAllocMaxInstances];
 
 extern "C" int faco_run_batch_noalloc(faco_instance *const *hs, int32_t count,
                                       int32_t iterations, void *hip_stream) {
@@ -1585,7 +1583,7 @@ extern "C" int faco_run_batch_noalloc(faco_instance *const *hs, int32_t count,
   int2 *d_amap = reinterpret_cast<int2 *>(base + kScratchInstBytes);
   std::lock_guard<std::mutex> lk(g_batch_mu);
   BatchShape B;
-  batch_shape(hs, count, g_na_insts, g_na_amap, g_batch_cfg, B);
+  batch_shape(hs, count, g_na_insts, g_na_amap, g_na_order, g_batch_cfg, B);
   BT(hipMemcpyAsync(d_insts, g_na_insts, sizeof(Inst) * (size_t)count, hipMemcpyHostToDevice,
                     st));
   BT(hipMemcpyAsync(d_amap, g_na_amap, sizeof(int2) * (size_t)B.total, hipMemcpyHostToDevice,

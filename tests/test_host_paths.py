@@ -31,3 +31,16 @@ F.faco_get_best_tour(h)
 print(json.dumps(dict(refused=refused, copies=copies, launches=ln)))
 """)
     assert got == {"refused": 19, "copies": 0, "launches": 0}
+
+
+def test_noalloc_batch_takes_no_host_memory(stub):
+    """Also for an uneven batch at the entry point's limit of 256 instances:
+    a failed allocation would leave the C entry point as a C++ exception."""
+    got = host_stub.run(stub, """
+hs = [build(20 + (37 * i) % 100, ants=4) for i in range(256)]
+arr = (ctypes.c_void_p * len(hs))(*[h.h for h in hs])
+S.stub_reset()
+rc = F.lib().faco_run_batch_noalloc(arr, len(hs), 3, None)
+print(json.dumps(dict(rc=rc, news=S.stub_news(), events=S.stub_events(), launches=S.stub_launch_count())))
+""")
+    assert got == {"rc": 0, "news": 0, "events": 0, "launches": 6}
