@@ -39,6 +39,7 @@ struct faco_instance {
   size_t lds_ant = 0;   // LDS of the per-iteration ant kernel
   size_t lds_init = 0;  // LDS of the initial solution's ant kernel (flat tour)
   int tw = 1;  // waves per ant in the per-instance ant kernel
+  int tw_init = 8;  // waves of the initial solution's kernel
   int device = 0;  // the device current at build
   std::vector<int32_t> orig_of, int_of;  // internal label <-> original city number
   std::vector<int32_t> xy_host;          // the build's coordinates (autotuner twins)
@@ -274,6 +275,14 @@ static int team_waves_for(int32_t ants, bool uneven = false) {
   return ants <= 2048 || uneven ? 4 : 1;
 }
 
+// Waves of the initial solution's kernel: one ant on an idle chip, whatever the
+// number of ants.  With the ants' own count a build of 10 000 cities took 13.3 ms
+// at 400 ants (4 waves) and 23.2 at 2049 (one) instead of 12.0.
+static int init_waves() {
+  std::lock_guard<std::mutex> lk(g_team_mu);
+  return g_team_waves ? g_team_waves : 8;
+}
+
 // Segment-list ant tours: 0 and 1 flat arrays (the default: on this GPU a
 // segment-list move costs as much as a flat rewrite of a typical move, and
 // every evaluation pays the record lookups), 2 segment lists; segment length
@@ -453,6 +462,7 @@ extern "C" int faco_build_instance(const int32_t *xy, int32_t n, const faco_para
 
   faco_instance *h = new faco_instance();
   h->tw = tw;
+  h->tw_init = init_waves();
   h->p = *p;
   h->n = n;
   h->xy_host.assign(xy, xy + 2 * (size_t)n);
@@ -616,12 +626,16 @@ extern "C" int faco_build_instance(const int32_t *xy, int32_t n, const faco_para
     return fail(FACO_EDUP);
   }
 
-  h->lds_init = sizeof(uint32_t) * ((size_t)faco_team_lds_words(h->tw) +
-                                    3 * (size_t)((n + 31) / 32) + (size_t)I.lcap);
-  BTRY(hipFuncSetAttribute((const void *)faco_ant_kernel(h->k, h->tw),
-                           hipFuncAttributeMaxDynamicSharedMemorySize, (int)h->lds_init));
-  h->lds_ant = h->lds_init;
-  if (I.seg_on) {
+  const size_t flat_words = 3 * (size_t)((n + 31) / 32) + (size_t)I.lcap;
+  h->lds_init = sizeof(uint32_t) * ((size_t)faco_team_lds_words(h->tw_init) + flat_words);
+  const AntKernelFn initk = faco_ant_kernel(h->k, h->tw_init);
+  BTRY(hipFuncSetAttribute((const void *)initk, hipFuncAttributeMaxDynamicSharedMemorySize,
+                           (int)h->lds_init));
+  if (!I.seg_on) {
+    h->lds_ant = sizeof(uint32_t) * ((size_t)faco_team_lds_words(h->tw) + flat_words);
+    BTRY(hipFuncSetAttribute((const void *)faco_ant_kernel(h->k, h->tw),
+                             hipFuncAttributeMaxDynamicSharedMemorySize, (int)h->lds_ant));
+  } else {
     h->lds_ant = sizeof(uint32_t) * ((size_t)faco_seg_lds_words(h->tw, n) +
                                      4 * (size_t)I.seg_max + (size_t)I.lcap);
     BTRY(hipFuncSetAttribute((const void *)faco_ant_seg_kernel(h->k, h->tw),
@@ -629,9 +643,8 @@ extern "C" int faco_build_instance(const int32_t *xy, int32_t n, const faco_para
   }
   // initial solution (ant slot 0, flat tour), limits, tau = tau_max, source =
   // global best
-  const AntKernelFn initk = faco_ant_kernel(h->k, h->tw);
   auto launch_init = [&](int mode) {
-    hipLaunchKernelGGL(initk, dim3(1), dim3(64 * h->tw), h->lds_init, h->stream, I, mode);
+    hipLaunchKernelGGL(initk, dim3(1), dim3(64 * h->tw_init), h->lds_init, h->stream, I, mode);
   };
   // the search in a launch per sweep; its end is looked for every few sweeps
   // (launches after it return at once).  Every launch before the end makes at
@@ -666,7 +679,7 @@ extern "C" int faco_build_instance(const int32_t *xy, int32_t n, const faco_para
     launch_init(1);
   } else {
     launch_init(2);
-    BTRY(search_chain(initk, h->tw, h->lds_init, faco_init_sweep_kernel(h->k), 256));
+    BTRY(search_chain(initk, h->tw_init, h->lds_init, faco_init_sweep_kernel(h->k), 256));
   }
   hipLaunchKernelGGL(faco::init_state_kernel, dim3(1), dim3(1), 0, h->stream, I);
   hipLaunchKernelGGL(faco::init_source_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0,

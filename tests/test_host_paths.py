@@ -44,3 +44,21 @@ rc = F.lib().faco_run_batch_noalloc(arr, len(hs), 3, None)
 print(json.dumps(dict(rc=rc, news=S.stub_news(), events=S.stub_events(), launches=S.stub_launch_count())))
 """)
     assert got == {"rc": 0, "news": 0, "events": 0, "launches": 6}
+
+
+def test_initial_solution_takes_a_team_whatever_the_ants(stub):
+    """One ant on an idle chip; a forced number of waves holds for it too."""
+    got = host_stub.run(stub, """
+out = []
+for tw, n, ants in [(0, 300, 16), (0, 300, 400), (0, 300, 4096), (0, 1500, 400), (1, 300, 16),
+                    (4, 1500, 16)]:
+    F.faco_set_team_waves(tw)
+    S.stub_reset()
+    h = build(n, ants=ants)
+    one = [L["block"][0] for L in launches() if L["grid"] == [1, 1, 1] and L["block"][0] > 1]
+    assert len(set(one)) == 1, one
+    out.append(one[0] // 64)
+    h.close()
+print(json.dumps(out))
+""")
+    assert got == [8, 8, 8, 8, 1, 4]
