@@ -222,8 +222,9 @@ static void end_timed(faco_instance *h, TimedLaunch &tl) {
   h->pending.push_back(tl);
 }
 
-// Waves per ant for instances built from now on (0 = by size: large tours
-// with few enough ants to leave the chip's wave slots to the teams).
+static const size_t kLdsBytes = 160 * 1024;  // LDS of one CU (gfx950)
+
+// Waves per ant for instances built from now on (0 = team_waves_for).
 static std::mutex g_team_mu;
 static int g_team_waves = 0;
 
@@ -264,7 +265,13 @@ static int queue_lds_cap_for(int32_t n, int extra_words = 0) {
 // 4-wave teams.  Per iteration with 8/4/1 waves (us): 200 cities and 16 ants
 // 136/139/164, 1000 and 256 272/280/456, 10 000 and 400 1278/1190/2339, 1000
 // and 1024 986/530/736, 1000 and 4096 3341/1320/1030.
-static int team_waves_for(int32_t ants, bool uneven = false) {
+// On segment lists a team gains less (the leader makes every decision of the
+// search too), and beyond 512 ants lone waves are faster wherever a CU's LDS
+// holds at least two ants: 8/4/1 waves, early iterations: 1000 cities and 512
+// ants 1119/749/734, 1024 ants 1727/956/750; 3000 and 768 1715/1222/975; 10 000
+// and 1024 2283/2393/1656; where it holds one (20 000 and 1024) 2488/2674/3190.
+// ant_words: LDS words of an ant beside its team area.
+static int team_waves_for(int32_t ants, size_t ant_words, bool seg, bool uneven = false) {
   int tw;
   {
     std::lock_guard<std::mutex> lk(g_team_mu);
@@ -272,6 +279,8 @@ static int team_waves_for(int32_t ants, bool uneven = false) {
   }
   if (tw) return tw;
   if (ants <= 256) return 8;
+  const size_t lone = kLdsBytes / (sizeof(uint32_t) * ant_words);
+  if (seg && ants > 512) return lone >= 2 ? 1 : 8;
   return ants <= 2048 || uneven ? 4 : 1;
 }
 
@@ -309,11 +318,11 @@ struct SegPlan {
   int on = 0, shift = 0, max = 0;
 };
 
-// Whether an instance of n cities whose ants have tw waves runs its local
-// search on segment lists, and with which segment length and record limit.
+// Whether an instance of n cities runs its local search on segment lists, and
+// with which segment length and record limit.
 // Auto length: the smallest power of two >= 64 that cuts the tour into at
 // most a quarter of the record table.
-static int seg_plan(int32_t n, int tw, SegPlan *sp) {
+static int seg_plan(int32_t n, SegPlan *sp) {
   int mode, lg, mx;
   {
     std::lock_guard<std::mutex> lk(g_team_mu);
@@ -322,7 +331,6 @@ static int seg_plan(int32_t n, int tw, SegPlan *sp) {
     mx = g_seg_max;
   }
   *sp = SegPlan{};
-  (void)tw;
   if (mode != 2) return FACO_OK;
   sp->on = 1;
   sp->max = mx ? mx : faco::kSegCap;
@@ -358,7 +366,7 @@ extern "C" uint64_t faco_footprint_bytes(int32_t n, const faco_params *p) {
   b += align_up(8 * A) + 2 * align_up(8 * A * faco::NCNT) + align_up(8 * faco::kTicks * A);
   b += align_up(4 * A);  // final tour buffer of each ant
   SegPlan sp;
-  if (seg_plan(n, team_waves_for(p->n_ants), &sp) == FACO_OK && sp.on)
+  if (seg_plan(n, &sp) == FACO_OK && sp.on)
     b += 2 * align_up(4 * N * A) + 2 * align_up(8 * N * A) + align_up(4 * A);  // segment lists
   b += align_up(4 * ((N + 31) / 32));      // marks of the initial search's sweeps
   b += 2 * align_up(8 * (A + 1)) + align_up(4 * (A + 1));  // verification
@@ -456,9 +464,12 @@ extern "C" int faco_build_instance(const int32_t *xy, int32_t n, const faco_para
   for (int64_t i = 0; i < 2 * (int64_t)n; ++i)
     if (xy[i] < 0 || xy[i] >= (1 << 26))
       return set_err(nullptr, FACO_EINVAL, "coordinates must be in [0, 2^26)");
-  const int tw = team_waves_for(p->n_ants);
   SegPlan sp;
-  if (int rc = seg_plan(n, tw, &sp)) return rc;
+  if (int rc = seg_plan(n, &sp)) return rc;
+  const int lcap = queue_lds_cap_for(n, sp.on ? 4 * sp.max : 0);
+  const int tw = team_waves_for(
+      p->n_ants, 3 * (size_t)((n + 31) / 32) + (size_t)lcap + (sp.on ? 4 * (size_t)sp.max : 0),
+      sp.on);
 
   faco_instance *h = new faco_instance();
   h->tw = tw;
@@ -488,7 +499,7 @@ extern "C" int faco_build_instance(const int32_t *xy, int32_t n, const faco_para
   I.seg_on = sp.on;
   I.seg_shift = sp.shift;
   I.seg_max = sp.max;
-  I.lcap = queue_lds_cap_for(n, sp.on ? 4 * sp.max : 0);
+  I.lcap = lcap;
   I.rho = p->rho;
   I.ls_flags = p->ls_flags;
   I.oropt_max = p->oropt_max_seg;
@@ -969,7 +980,6 @@ extern "C" int faco_phase_times(faco_instance *h, double *ms_out, int64_t *launc
 // faco_autotune_batch stored for the batch's size class, else the
 // process-wide default.  None of it changes a result.
 
-static const size_t kLdsBytes = 160 * 1024;  // LDS of one CU (gfx950)
 static std::mutex g_batch_mu;
 static faco_batch_config g_batch_cfg = {0, 0, 1, 0, 0, 0};
 // tuned configurations by size class (log2 of the longest tour)
@@ -1093,7 +1103,6 @@ static void batch_shape(faco_instance *const *hs, int32_t count, Inst *insts, in
   int64_t sum_n = 0;
   for (int32_t i = 0; i < count; ++i) sum_n += hs[i]->n;
   const bool uneven = 2 * sum_n < (int64_t)B.maxn * count;
-  B.tw = cfg.team_waves ? cfg.team_waves : team_waves_for(B.total, uneven);
   for (int32_t i = 0; i < count; ++i) {
     faco_instance *h = hs[i];
     insts[i] = h->dv;
@@ -1109,6 +1118,7 @@ static void batch_shape(faco_instance *const *hs, int32_t count, Inst *insts, in
     const unsigned ub = faco::update_blocks(h->n, h->dv.ks);
     B.max_update = ub > B.max_update ? ub : B.max_update;
   }
+  B.tw = cfg.team_waves ? cfg.team_waves : team_waves_for(B.total, B.lds_words, false, uneven);
   // workgroups start in table order: the longest tours' ants first, so that
   // the launch does not end on one of them
   for (int32_t i = 0; i < count; ++i) order[i] = i;

@@ -62,3 +62,33 @@ for tw, n, ants in [(0, 300, 16), (0, 300, 400), (0, 300, 4096), (0, 1500, 400),
 print(json.dumps(out))
 """)
     assert got == [8, 8, 8, 8, 1, 4]
+
+
+WAVES = """
+out = []
+for n, ants, kw in %s:
+    F.faco_set_tour_segments(kw.get("seg", 0))
+    h = build(n, ants=ants)
+    S.stub_reset()
+    F.faco_run_iterations(h, 1)
+    L = launches()[0]
+    assert L["grid"][0] == ants and L["lds"] <= 160 * 1024
+    assert int(F.faco_debug_get(h, F.FACO_DBG_TEAM_WAVES)[0]) * 64 == L["block"][0]
+    out.append(L["block"][0] // 64)
+    h.close()
+print(json.dumps(out))
+"""
+
+
+def _waves(stub, cases):
+    got = host_stub.run(stub, WAVES % repr([c[:3] for c in cases]))
+    assert got == [c[3] for c in cases], list(zip(cases, got))
+
+
+def test_waves_of_segment_list_ants(stub):
+    """Teams up to 512 ants; beyond, lone waves while a CU's LDS holds two ants,
+    else teams of 8 (one ant a CU either way)."""
+    seg = dict(seg=2)
+    _waves(stub, [(300, 256, seg, 8), (300, 257, seg, 4), (300, 512, seg, 4),
+                  (300, 513, seg, 1), (300, 4096, seg, 1), (3000, 600, seg, 1),
+                  (10000, 600, seg, 1), (14000, 600, seg, 8)])
