@@ -260,11 +260,22 @@ static int queue_lds_cap_for(int32_t n, int extra_words = 0) {
   return cap < room ? cap : room;
 }
 
-// Waves per ant by the number of ants in flight: a team shortens an ant's
-// chain at every size, but a CU holds one 8-wave team (its registers) or four
-// 4-wave teams.  Per iteration with 8/4/1 waves (us): 200 cities and 16 ants
-// 136/139/164, 1000 and 256 272/280/456, 10 000 and 400 1278/1190/2339, 1000
-// and 1024 986/530/736, 1000 and 4096 3341/1320/1030.
+// Waves per ant by the ants in flight and the LDS they take: a team shortens an
+// ant's chain at every size, but a CU holds one 8-wave team (its registers) and
+// as many 4-wave teams as its registers (four) and its LDS allow.
+//   up to 256 ants, one a CU: 8.  Per iteration with 8/4/1 waves (us; early
+//     iterations, lists of 16): 200 cities and 256 ants 219/235/346, 10 000 and
+//     256 385/415/668; with 300 ants 253/240/345 and 435/418/665.
+//   LDS for one 4-wave team a CU only (tours from about 16 300 cities on with the
+//     default queue): 8 at any number of ants.  300/1024/2100 ants: 16 000 cities
+//     508/1126/2008 with 8 and 492/863/1398 with 4 waves, 16 600 cities
+//     568/1100/2056 and 632/1222/2298 (one wave 899/1290/2175).
+//   up to 2048 ants: 4.  1000 cities and 1024 ants 834/444/529, 10 000 and 2048
+//     1895/1301/1444.
+//   beyond: lone waves, which hold more ants a CU.  1000 cities and 4096 ants
+//     2922/1237/830, 5000 3302/1416/1285; the lines cross between 1024 and 2048
+//     ants for tours below 2000 cities (2048 ants of 1000: 720 with 4, 658 with 1)
+//     and beyond 4096 for 10 000 (2281 and 2432).
 // On segment lists a team gains less (the leader makes every decision of the
 // search too), and beyond 512 ants lone waves are faster wherever a CU's LDS
 // holds at least two ants: 8/4/1 waves, early iterations: 1000 cities and 512
@@ -279,8 +290,12 @@ static int team_waves_for(int32_t ants, size_t ant_words, bool seg, bool uneven 
   }
   if (tw) return tw;
   if (ants <= 256) return 8;
-  const size_t lone = kLdsBytes / (sizeof(uint32_t) * ant_words);
-  if (seg && ants > 512) return lone >= 2 ? 1 : 8;
+  // ants of w waves that a CU's LDS holds
+  auto resident = [&](int w) {
+    return kLdsBytes / (sizeof(uint32_t) * ((size_t)faco_team_lds_words(w) + ant_words));
+  };
+  if (seg && ants > 512) return resident(1) >= 2 ? 1 : 8;
+  if (resident(4) < 2) return 8;
   return ants <= 2048 || uneven ? 4 : 1;
 }
 

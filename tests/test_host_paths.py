@@ -92,3 +92,12 @@ def test_waves_of_segment_list_ants(stub):
     _waves(stub, [(300, 256, seg, 8), (300, 257, seg, 4), (300, 512, seg, 4),
                   (300, 513, seg, 1), (300, 4096, seg, 1), (3000, 600, seg, 1),
                   (10000, 600, seg, 1), (14000, 600, seg, 8)])
+
+
+def test_waves_of_ants_by_lds(stub):
+    """Long tours: LDS holds one 4-wave team a CU from about 16 300 cities on
+    (with the default queue), so the ants take teams of 8 at any number."""
+    flat = {}
+    _waves(stub, [(16200, 256, flat, 8), (16200, 300, flat, 4), (16400, 300, flat, 8),
+                  (4000, 2048, flat, 4), (4000, 2049, flat, 1), (17000, 2049, flat, 8),
+                  (30000, 300, flat, 8)])
