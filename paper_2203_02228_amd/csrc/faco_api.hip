@@ -1155,6 +1155,23 @@ static void batch_shape(faco_instance *const *hs, int32_t count, Inst *insts, in
   B.persistent = cfg.persistent == 1 && !B.any_verify;
 }
 
+// Workgroups of a persistent launch per CU, at most.  Every ant begins with an
+// acquire and ends with a release at device scope, an invalidation and a
+// write-back of its XCD's L2 that the ants beside it pay for: more ants at once
+// are not always more ants a second.  Iterations with one wave a SIMD (four lone
+// waves or a 4-wave team a CU) and with two, in us:
+//   lone waves: 128 instances of 200..5000 cities, 16 ants each, 4683 and 9837;
+//     256 of 1000 3982 and 10 475; 600 of 200 6093 and 9157
+//   4-wave teams: 64 of 200 626 and 949; 64 of 200..5000 1002 and 1235; 16 of
+//     4000..16 000, 32 ants each, 1890 and 2578; 40 of them 2326 and 3481; 96 of
+//     200..5000, 16 ants each, 1448 and 1401; 128 1871 and 1574; 256 3521 and 2784
+// so lone waves stay at one a SIMD, and 4-wave teams up to 6 ants a CU.  (8-wave
+// teams fill a CU with one.)
+static int persist_workers_per_cu(const BatchShape &B, int ncu) {
+  if (B.tw == 1) return 4 / B.apb;
+  return B.tw == 4 && B.total > 6 * ncu ? 2 : 1;
+}
+
 // The launches of one batched iteration over the device tables.
 static void enqueue_batch_iteration(const BatchShape &B, const Inst *d_insts,
                                     const int2 *d_amap, hipStream_t s) {
@@ -1252,7 +1269,8 @@ static int run_batch_one(faco_instance *const *hs, int32_t count, int32_t iterat
     BT(hipMemcpyAsync(g_ws.run, &run, sizeof(run), hipMemcpyHostToDevice, st));
     BT(hipFuncSetAttribute((const void *)B.persk, hipFuncAttributeMaxDynamicSharedMemorySize,
                            (int)B.lds_bytes));
-    // as many workers as can be resident, at most one per ant
+    // as many workers as persist_workers_per_cu allows and can be resident, at most
+    // one per ant
     const int threads = 64 * (B.tw > 1 ? B.tw : B.apb);
     int per_cu = 0, dev = 0, ncu = 0;
     BT(hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, (const void *)B.persk, threads,
@@ -1260,7 +1278,10 @@ static int run_batch_one(faco_instance *const *hs, int32_t count, int32_t iterat
     BT(hipGetDevice(&dev));
     BT(hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, dev));
     const int want = B.tw > 1 ? total : (total + B.apb - 1) / B.apb;
-    int grid = (per_cu > 0 ? per_cu : 1) * (ncu > 0 ? ncu : 1);
+    ncu = ncu > 0 ? ncu : 1;
+    const int most = persist_workers_per_cu(B, ncu);
+    per_cu = per_cu < most ? per_cu : most;
+    int grid = (per_cu > 0 ? per_cu : 1) * ncu;
     grid = grid < want ? grid : want;
     hipLaunchKernelGGL(B.persk, dim3((unsigned)grid), dim3((unsigned)threads), B.lds_bytes, st,
                        (const Inst *)g_ws.insts, g_ws.ctl, g_ws.run, (int)B.lds_words);

@@ -101,3 +101,23 @@ def test_waves_of_ants_by_lds(stub):
     _waves(stub, [(16200, 256, flat, 8), (16200, 300, flat, 4), (16400, 300, flat, 8),
                   (4000, 2048, flat, 4), (4000, 2049, flat, 1), (17000, 2049, flat, 8),
                   (30000, 300, flat, 8)])
+
+
+def test_workers_of_persistent_batches(stub):
+    """One wave a SIMD, and two with 4-wave teams beyond 6 ants a CU (256 CUs,
+    room for 8 workgroups on each)."""
+    got = host_stub.run(stub, """
+out = []
+for tw, apb, count, ants in [(1, 1, 16, 256), (1, 1, 10, 64), (1, 2, 16, 256), (1, 4, 16, 256),
+                             (4, 1, 6, 256), (4, 1, 7, 256), (4, 1, 3, 64), (8, 1, 16, 64)]:
+    F.faco_set_batch_config(persistent=1, team_waves=tw, ants_per_block=apb,
+                            queue_lds_capacity=64)
+    hs = [build(40, ants=ants) for _ in range(count)]
+    S.stub_reset()
+    F.faco_run_batch(hs, 3)
+    (L,) = launches()
+    assert L["block"][0] == 64 * max(tw, apb)
+    out.append(L["grid"][0])
+print(json.dumps(out))
+""")
+    assert got == [1024, 640, 512, 256, 256, 512, 192, 256]
