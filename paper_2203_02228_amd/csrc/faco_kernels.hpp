@@ -589,15 +589,15 @@ FACO_DEV bool has_improving(const Inst &I, uint32_t flags, int x, const FlatT &T
 
 #include "faco_seg.hpp"
 
-// 64-element chunks in flight per wave and round of a rewrite.  More hide more
-// of a long rewrite's latency and take eight registers each: 8-wave teams (one
-// ant per CU, long tours) hold 16, which keeps 2 waves per SIMD; 4-wave teams
-// 8 and lone waves 4, so that the many ants of a batch run beside each other
-// (4 waves per SIMD with 4-wave teams).  A batch of 64 instances of 200..5000
-// cities takes 0.71 ms an iteration on 4-wave teams with 8 chunks and 0.83 with
-// 16; a 100k run 4.25 ms on 8-wave teams with 16 and 4.28 with 8.
+// 64-element chunks in flight per wave and round of a team's rewrite.  More hide
+// more of a long rewrite's latency and take eight registers each: 8-wave teams,
+// one a CU at any tour length, hold 16, which keeps 2 waves per SIMD; 4-wave teams
+// 8, so that the many ants of a batch run beside each other (4 waves per SIMD).  A
+// batch of 64 instances of 200..5000 cities takes 0.71 ms an iteration on 4-wave
+// teams with 8 chunks and 0.83 with 16; a 100k run 4.25 ms on 8-wave teams with 16
+// and 4.28 with 8.  (Lone waves: see lone_reverse.)
 template <int TW>
-constexpr int team_chunks() { return TW == 8 ? 16 : (TW == 4 ? 8 : 4); }
+constexpr int team_chunks() { return TW == 8 ? 16 : 8; }
 
 // Reverse the cyclic array range of length L starting at s: pairs (i,
 // L-1-i) are disjoint, so the 64-pair chunks are dealt to the waves of a
@@ -678,6 +678,25 @@ FACO_DEV void shift_part(int n, int src, int dst, int D, bool down, int w, int32
   }
 }
 
+// Rewrites by a lone wave: 4 chunks in flight, and 8 where that leaves rounds.  8
+// throughout cost batches of short tours 1..3% (256 instances of 200..5000 cities
+// 1322 against 1289 us an iteration); 4 throughout cost long tours 1..4% (200 000
+// cities, lists of 12, 4.46 against 4.28 ms).
+constexpr int kLoneShort = 4 * kWave;
+FACO_DEV void lone_reverse(int n, int s, int L, int32_t *route, int32_t *pos, int2 *rxy) {
+  if (L >> 1 <= kLoneShort)
+    reverse_part<1, 4>(n, s, L, 0, route, pos, rxy);
+  else
+    reverse_part<1, 8>(n, s, L, 0, route, pos, rxy);
+}
+FACO_DEV void lone_shift(int n, int src, int dst, int D, bool down, int32_t *route, int32_t *pos,
+                         int2 *rxy) {
+  if (D <= kLoneShort)
+    shift_part<1, 4>(n, src, dst, D, down, 0, route, pos, rxy);
+  else
+    shift_part<1, 8>(n, src, dst, D, down, 0, route, pos, rxy);
+}
+
 // "Flip a section between x and y": the shorter of the paths x..y and z..w.
 // px, py, pz: array positions of x, y, z.
 FACO_DEV int apply_2opt(int n, int px, int py, int pz, int32_t *route, int32_t *pos,
@@ -685,7 +704,7 @@ FACO_DEV int apply_2opt(int n, int px, int py, int pz, int32_t *route, int32_t *
   const int L1 = wrapc(py - px, n) + 1;
   const bool first = 2 * L1 <= n;
   const int L = first ? L1 : n - L1;
-  reverse_part<1>(n, first ? px : pz, L, 0, route, pos, rxy);
+  lone_reverse(n, first ? px : pz, L, route, pos, rxy);
   wave_fence();
   return L;
 }
@@ -724,7 +743,7 @@ FACO_DEV int apply_oropt(int n, int L, int a, int f, int b, int e, int side,
   int moved;
   if (D1 <= D2) {
     // block q..x1 moves back by L to start at fpos; segment follows it
-    shift_part<1>(n, pq, fpos, D1, true, 0, route, pos, rxy);
+    lone_shift(n, pq, fpos, D1, true, route, pos, rxy);
     wave_fence();
     if (lane < L) {
       const int d = wrapc(fpos + D1 + lane, n);
@@ -735,7 +754,7 @@ FACO_DEV int apply_oropt(int n, int L, int a, int f, int b, int e, int side,
     moved = D1 + L;
   } else {
     // block x2..p moves forward by L; segment goes in front of it
-    shift_part<1>(n, px2, wrap1(px2 + L, n), D2, false, 0, route, pos, rxy);
+    lone_shift(n, px2, wrap1(px2 + L, n), D2, false, route, pos, rxy);
     wave_fence();
     if (lane < L) {
       const int d = wrap1(px2 + lane, n);
