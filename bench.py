@@ -445,6 +445,13 @@ def slowest_ants(F, stream, w, warmup, steps, torch):
     return {"slowest": avg(slow), "median": avg(med)}
 
 
+def phase_means(phase_ms, launches):
+    """Mean milliseconds of an iteration's launches, by name (faco_phase_times:
+    slot 0 the ants, slot 3 the whole update, one launch)."""
+    return {name: round(phase_ms[i] / max(1, launches[i]), 4)
+            for name, i in (("ants", 0), ("update", 3))}
+
+
 def full_run(F, I, torch, stream, w):
     """The configured run: all of the workload's iterations from a fresh build,
     with every tour length recomputed and checked on the device in every
@@ -578,7 +585,8 @@ def main():
              [(0, "construct"), (1, "ls_eval"), (2, "ls_apply"), (3, "sweep"), (4, "ant_total"),
               (8, "spec_windows"), (9, "one_steps"), (10, "copies"), (11, "fallbacks"),
               (13, "ls_eval_oropt"), (15, "ls_rewrite"), (24, "sweep_tests"),
-              (25, "sweep_listing")]}
+              (25, "sweep_listing")]
+             if i != 13 or per[13] > 0}  # counted apart by lone waves and on segment lists only
     tk_calls = {name: round(float(per[i]), 1) for i, name in
                 [(5, "spec_windows"), (6, "one_steps"), (7, "copies"), (12, "eval_rounds"),
                  (14, "oropt_rounds"), (26, "sweep_cities")]}
@@ -646,9 +654,7 @@ def main():
         "slowest_ant_us": slowest_us,
         "segment_lists": seg_stats,
         "per_ant_counters": {name: round(v, 1) for name, v in zip(F.CNT_NAMES, cnt_mean)},
-        "phase_ms_per_iteration": {name: round(phase_ms[i] / max(1, launches[i]), 4)
-                                   for i, name in enumerate(["ants", "colony", "source",
-                                                             "pheromone"])},
+        "phase_ms_per_iteration": phase_means(phase_ms, launches),
         "roofline": {"bound": "hbm", "achieved": round(achieved, 2), "peak": HBM_PEAK_GBS,
                      "unit": "GB/s", "frac": round(achieved / HBM_PEAK_GBS, 5),
                      "traffic": traffic, "kernel": "ant_kernel",
