@@ -956,8 +956,9 @@ extern "C" int faco_set_timing(faco_instance *h, int32_t enable) {
   if (!h) return set_err(nullptr, FACO_EINVAL, "handle is NULL");
   if (enable < 0) return set_err(h, FACO_EINVAL, "enable must be >= 0");
   h->timing = enable != 0;
-  // events for `enable` iterations (two per phase) made ahead of the launches
-  const size_t want = enable > 1 ? (size_t)enable * 8 : 0;
+  // events for `enable` iterations (two for each of their two timed launches)
+  // made ahead of the launches
+  const size_t want = enable > 1 ? (size_t)enable * 4 : 0;
   while (h->ev_pool.size() < want) {
     hipEvent_t e;
     HIP_TRY(h, hipEventCreate(&e));

@@ -121,3 +121,17 @@ for tw, apb, count, ants in [(1, 1, 16, 256), (1, 1, 10, 64), (1, 2, 16, 256), (
 print(json.dumps(out))
 """)
     assert got == [1024, 640, 512, 256, 256, 512, 192, 256]
+
+
+def test_events_reserved_for_timed_iterations(stub):
+    """Two events for each of an iteration's two launches, and none made while
+    the reserved iterations are enqueued."""
+    got = host_stub.run(stub, """
+h = build(60)
+S.stub_reset()
+F.faco_set_timing(h, True, reserve_iterations=10)
+made = S.stub_events()
+F.faco_run_iterations(h, 10)
+print(json.dumps([made, S.stub_events() - made]))
+""")
+    assert got == [40, 0]
