@@ -135,3 +135,24 @@ F.faco_run_iterations(h, 10)
 print(json.dumps([made, S.stub_events() - made]))
 """)
     assert got == [40, 0]
+
+
+def test_waves_of_default_batches(stub):
+    """Few ants 8, up to 2048 4; beyond, 1 for even tours and 4 where the mean
+    length is below half the longest; 8 where LDS holds one 4-wave team a CU."""
+    got = host_stub.run(stub, """
+out = []
+for sizes, ants in [([60, 500, 900], 16), ([60] * 4, 64), ([60] * 5, 64), ([60] * 32, 64),
+                    ([60] * 33, 64), ([200] + [98] * 32, 64), ([200] + [96] * 32, 64),
+                    ([16200, 50, 50], 100), ([16400, 50, 50], 100)]:
+    hs = [build(n, ants=ants) for n in sizes]
+    S.stub_reset()
+    F.faco_run_batch(hs, 1)
+    L = launches()[0]
+    assert L["grid"][0] == ants * len(sizes) and L["lds"] <= 160 * 1024
+    out.append(L["block"][0] // 64)
+    for h in hs:
+        h.close()
+print(json.dumps(out))
+""")
+    assert got == [8, 8, 4, 4, 1, 1, 4, 4, 8]
