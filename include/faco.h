@@ -178,7 +178,7 @@ typedef struct faco_batch_config {
                                  captured as a HIP graph and replayed.
                                  Instances with verification on run per
                                  phase.                                     */
-  int32_t team_waves;         /* waves per ant: 0 = by the number of ants
+  int32_t team_waves;         /* waves per ant: 0 = by the ants and their LDS
                                  (faco_set_team_waves), else 1, 4 or 8      */
   int32_t ants_per_block;     /* one-wave ants per workgroup: 1, 2 or 4,
                                  lowered when their LDS would not fit a CU  */
@@ -228,7 +228,10 @@ int faco_set_batch_ants_per_block(int32_t ants_per_block);
  * for faco_run_batch launches after it (process-wide): 1, 4 or 8, or 0 for a
  * choice by the number of ants (8 up to 256, 4 up to 2048, 1 beyond; a batch
  * counts all its ants, and takes 4 beyond 2048 too while its tours' mean
- * length is below half the longest).  Wave 0 of an ant makes every decision of
+ * length is below half the longest) and their LDS: 8 where a CU's LDS holds
+ * one ant of 4 waves only (tours from about 16 300 cities on), and for
+ * segment lists with more than 512 ants 1, or 8 where it holds one ant of one
+ * wave only.  The initial solution takes 8, or what is set here.  Wave 0 of an ant makes every decision of
  * the construction and the others share its wide steps (speculative
  * source-following windows, copies, nearest-city scans); the local search is
  * run by all waves (a listed city each, the array rewrites, sweep tests).  An

@@ -235,8 +235,9 @@ FACO_DEV int nint_sqrt(double d2) {
   return (int)r + (e < -r ? 1 : 0) - (e >= r && r > 0.0 ? 1 : 0);
 }
 
-// cost() of two points that differ (0 and -1 are both possible for equal
-// ones): without the guard that r is positive.
+// cost() of two points that differ: without the guard that r is positive.  Equal
+// points give -1; no caller uses that value (it belongs to lanes or variants that
+// are masked, and a build with two cities at one place is refused).
 FACO_DEV int cost_ne(int2 a, int2 b) {
   const double dx = (double)(a.x - b.x), dy = (double)(a.y - b.y);
   const double d2 = __builtin_fma(dx, dx, dy * dy);

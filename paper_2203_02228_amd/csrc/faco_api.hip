@@ -464,10 +464,11 @@ static void hilbert_labels(const int32_t *xy, int32_t n, std::vector<int32_t> &o
 }
 
 // Initial searches of at least this many cities run their sweeps as launches
-// over the whole chip.  A sweep by the search's own workgroup costs 57 ns a
-// city (8 waves), a launch and the search's next one about 40 us together:
-// builds of 1500 cities 4.53 against 4.62 ms, of 5000 9.4 against 10.1, of
-// 100 000 173 against 547 (66 sweeps); of 700 both 3.56 ms.
+// over the whole chip.  A sweep by the search's own workgroup grows with the
+// tour, the launches of a sweep and the search's next part do not.  Builds with
+// launches against one launch, in us: 256 cities 558 and 515, 512 853 and 809, 850
+// 1206 and 1188, 1023 1293 and 1271, 1024 (other cities) 1607 and 1648, 1200 1720
+// and 1808, 2000 2628 and 2830, 3000 3787 and 4004.
 static const int32_t kChipSweepMin = 1024;
 
 extern "C" int faco_build_instance(const int32_t *xy, int32_t n, const faco_params *p,

@@ -81,7 +81,9 @@ struct Inst {
   int32_t *src_route, *src_pos;
   int32_t *gb_route;  // right behind *st, in one block: both are read in one copy
   int32_t *gb_pos;
-  int2 *src_adj;      // [n] (successor, predecessor) of each city in the source
+  int2 *src_adj;      // [n] (successor, predecessor) of each city in the source: written
+                      // and read by run_source and run_pheromone only (the persistent
+                      // form; the update launch reads the chosen tour itself)
   // Candidate rows in SOURCE order (row p = candidates of the city at source
   // position p), rewritten by the update kernel every iteration; laid out
   // by srow() in blocks of 64 positions, ks slots per row (those past k hold

@@ -101,9 +101,10 @@ struct TeamLds {
   int op;
   int arg[11];
   uint64_t arg64[2];
-  int f[2 * kMaxTeam];           // per-wave first stop (window, copy: by round parity)
-  int res[4];                    // window: last followed city; decision v, dv, pv
-  int64_t part[kMaxTeam];        // window: per-wave sums of source edge costs
+  int f[2 * kMaxTeam];           // window: per-wave first stop, by round parity; nearest: per-wave
+                                 // original number and index; sweep: per-wave counts
+  int res[4];                    // window: [1] the choice that ended it
+  int64_t part[kMaxTeam];        // nearest: per-wave distances; length: per-wave cost sums
   int64_t ub[kMaxTeam];          // nearest: per-wave bounds
   int cities[kMaxTeam * kWave];  // sweep: the batch of cities to test
   int disp[4];                   // persistent batches: the next task
@@ -1551,7 +1552,13 @@ __global__ void __launch_bounds__(256) init_sweep_kernel(Inst I) {
   }
 }
 
-// One workgroup of TW waves per ant.
+// One workgroup of TW waves per ant.  4-wave teams on flat arrays are held to 128
+// registers (here and in ant_batch_kernel), so that a CU runs four of them; with
+// lists of 12/16/24/32, 1000 cities and 1024 ants take 497/442/509/565 us an
+// iteration, and 574/510/682/747 without the bound.  It spills 2 to 36 registers
+// (most with long lists), which costs where a CU gets no four teams anyhow: 10 000
+// cities and 1000 ants (LDS holds three) 756/770/822/917 against 754/752/790/880, a
+// batch of 20 of 4000..16 000 cities 603/597/660/752 against 583/571/627/692.
 template <int KT, int TW, bool SEG = false>
 __global__ void __launch_bounds__(64 * TW, TW == 4 && !SEG ? 4 : 1) ant_kernel(Inst I, int mode) {
   extern __shared__ uint32_t lds[];

@@ -1,7 +1,8 @@
 // faco_update.hpp -- the per-instance update after the ants (colony: iteration
 // best, global best + limits, source choice; source materialisation; Eq. (2)
-// pheromone update) as device functions, shared by the per-phase kernels and
-// the persistent batched kernel.
+// pheromone update) as device functions: run_update for the update launch (lone
+// and batched), run_colony, run_source and run_pheromone for the persistent batched
+// kernel, the last two also for the state before the first iteration.
 #pragma once
 #include "device_common.hpp"
 #include "faco_device.hpp"
@@ -174,8 +175,9 @@ FACO_DEV void run_pheromone(const Inst &I, uint32_t slot, int init) {
 // ===================================================================== //
 // The whole update of an iteration in one launch (block `block` of
 // update_blocks()): every block makes the colony's decision for itself from
-// the ants' lengths, the first blocks update the pheromone and the padded rows
-// by (city, slot), the rest materialise the source by position.  Both read the
+// the ants' lengths, the first blocks update the pheromone, the padded rows and
+// the source's inverse by (city, slot), the rest write the source's route, edge
+// costs, coordinates and boxes by position.  Both read the
 // chosen tour's own arrays (route and pos of the iteration best, or of the
 // global best), so no block waits for another.  The state all blocks read is
 // written by the last block that has read it.  As three dependent launches the

@@ -261,7 +261,8 @@ def faco_set_tour_segments(mode, length_log2=0, max_records=0):
 
 
 def faco_set_team_waves(tw):
-    """Waves per ant for instances built afterwards (0 = by size; 1, 4, 8)."""
+    """Waves per ant for instances built afterwards (1, 4, 8; 0 = by the number of
+    ants and the LDS they take)."""
     _check(lib().faco_set_team_waves(int(tw)))
 
 
