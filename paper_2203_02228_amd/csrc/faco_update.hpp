@@ -182,17 +182,28 @@ FACO_DEV void run_pheromone(const Inst &I, uint32_t slot, int init) {
 // global best), so no block waits for another.  The state all blocks read is
 // written by the last block that has read it.  As three dependent launches the
 // update cost two more gaps of 7 us an iteration.  The decision takes a block
-// about 2 us, so large instances have a thread take several slots.
+// about 2 us, and the blocks count themselves off at one address (about 13 ns
+// each), so larger instances have a thread take several slots.  The launch with at
+// most 256 + 64, 512 + 128 and 1024 + 256 blocks, lists of 16, in us: 10 000 cities
+// 11.5/13.9/15.1, 20 000 13.6/16.1/21.0, 50 000 22.5/20.1/24.8, 100 000
+// 37.8/27.1/30.2, 200 000 67.5/43.5/41.7 (the three launches 20.8, 22.8, 29.6, 39.7
+// and 60.8): 512 + 128 until threads have 8 slots and 4 positions.
 // ===================================================================== //
 constexpr int kUpdateBlock = 256;
-constexpr unsigned kSlotBlocks = 1024, kPosBlocks = 256;
+// blocks for `items` threads: one each, but at most `lo` of them while a thread has
+// up to `most` items, and `hi` altogether
+__host__ __device__ inline unsigned update_part(unsigned items, unsigned most, unsigned lo,
+                                                unsigned hi) {
+  const unsigned all = (items + kUpdateBlock - 1) / kUpdateBlock;
+  unsigned cap = items / (most * kUpdateBlock);
+  cap = cap < lo ? lo : (cap > hi ? hi : cap);
+  return all < cap ? all : cap;
+}
 __host__ __device__ inline unsigned update_slot_blocks(int n, int ks) {
-  const unsigned b = ((unsigned)n * (unsigned)ks + kUpdateBlock - 1) / kUpdateBlock;
-  return b < kSlotBlocks ? b : kSlotBlocks;
+  return update_part((unsigned)n * (unsigned)ks, 8, 512, 1024);
 }
 __host__ __device__ inline unsigned update_pos_blocks(int n) {
-  const unsigned b = ((unsigned)n + kUpdateBlock - 1) / kUpdateBlock;
-  return b < kPosBlocks ? b : kPosBlocks;
+  return update_part((unsigned)n, 4, 128, 256);
 }
 __host__ __device__ inline unsigned update_blocks(int n, int ks) {
   return update_slot_blocks(n, ks) + update_pos_blocks(n);

@@ -156,3 +156,19 @@ for sizes, ants in [([60, 500, 900], 16), ([60] * 4, 64), ([60] * 5, 64), ([60] 
 print(json.dumps(out))
 """)
     assert got == [8, 8, 4, 4, 1, 1, 4, 4, 8]
+
+
+def test_blocks_of_the_update(stub):
+    """A block per 256 slots and per 256 positions, at most 512 and 128 while a
+    thread has up to 8 slots and 4 positions, then up to 1024 and 256."""
+    got = host_stub.run(stub, """
+out = []
+for n, k in [(300, 5), (8192, 16), (8193, 16), (33000, 4), (70000, 16), (150000, 16)]:
+    h = build(n, ants=2, k=k)
+    S.stub_reset()
+    F.faco_run_iterations(h, 1)
+    out.append(launches()[1]["grid"][0])
+    h.close()
+print(json.dumps(out))
+""")
+    assert got == [10 + 2, 512 + 32, 512 + 33, 512 + 128, 546 + 128, 1024 + 146]
